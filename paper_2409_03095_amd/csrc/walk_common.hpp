@@ -52,46 +52,46 @@ __device__ __forceinline__ void scan_bucket(const int32_t k[4], int32_t key, int
     }
 }
 
-// lds_add for a table one wavefront owns, whose bucket b0 (the key's home bucket)
-// was read into kp earlier, while the previous step's bucket load was in flight.
-// A copy that has gone stale is safe: keys never move, slots fill lowest first,
-// so a key missing from the copy is either absent or in a slot the copy shows
-// empty, and the compare-and-swap of the copy's first empty slot then reports it.
-__device__ __forceinline__ bool lds_add_pre(int32_t *keys, double *vals, uint32_t mask, uint32_t b0,
-                                            const int32_t kp[4], int32_t key, double w) {
-    uint32_t b = b0;
+// The slot of a bucket copy that `key` belongs in: the lowest one that holds it or
+// is empty (4: the bucket is full of other keys). Slots fill lowest first and
+// never empty, so that one search serves hits and insertions. Keys are
+// non-negative and an empty slot is -1, so k ^ key is 0 on a hit, negative on an
+// empty slot and positive on another key: one signed compare per slot.
+__device__ __forceinline__ int pick_slot(const int32_t k[4], int32_t key) {
+    int s = 4;
+#pragma unroll
+    for (int i = 3; i >= 0; --i) s = (k[i] ^ key) <= 0 ? i : s;
+    return s;
+}
+
+// lds_add for a table one wavefront owns, whose bucket b (the key's home bucket)
+// was read into k earlier, while the previous step's bucket load was in flight.
+// Hits and insertions take the same path (a compare-and-swap, which leaves a slot
+// that holds the key as it is): some lane of a wave inserts in most steps, so that
+// separate paths would both run (160^3 27-point walk 57.1 -> 55.3 ms, 128-chain
+// batched walk 24.9 -> 23.3 ms, 77^3 binary64 walk 9.8 -> 9.0 ms; a branch around
+// the compare-and-swap of hits: 59 ms). A copy that has gone stale is safe: keys never
+// move, slots fill lowest first, so the copy's slot for the key either is right or
+// has been taken by another key, which the compare-and-swap reports.
+__device__ __forceinline__ bool lds_add_pre(int32_t *keys, double *vals, uint32_t mask, uint32_t b, int32_t k[4],
+                                            int32_t key, double w) {
     int nb = 0;
-    bool first = true;
-    while (nb < kMaxLdsProbe / 4) {
-        int32_t k[4];
-        if (first) {
-            k[0] = kp[0];
-            k[1] = kp[1];
-            k[2] = kp[2];
-            k[3] = kp[3];
+#pragma unroll 1
+    for (;;) {
+        const int s = pick_slot(k, key);
+        if (s < 4) {
+            const int32_t prev = atomicCAS(&keys[b + s], kEmpty, key);
+            if ((prev ^ key) <= 0) {
+                atomicAdd(&vals[b + s], w);
+                return true;
+            }
+            // another key took the slot: read the bucket again
         } else {
-            read_bucket_wave(keys, b, k);
-        }
-        first = false;
-        int hit, emp;
-        scan_bucket(k, key, hit, emp);
-        if (hit >= 0) {
-            atomicAdd(&vals[b + hit], w);
-            return true;
-        }
-        if (emp < 0) {
             b = (b + 4u) & mask;
-            ++nb;
-            continue;
+            if (++nb >= kMaxLdsProbe / 4) return false;
         }
-        const int32_t prev = atomicCAS(&keys[b + emp], kEmpty, key);
-        if (prev == kEmpty || prev == key) {
-            atomicAdd(&vals[b + emp], w);
-            return true;
-        }
-        // another key took the slot: read the bucket again
+        read_bucket_wave(keys, b, k);
     }
-    return false;
 }
 
 // Adds w to key's slot, inserting the key if absent; false when the kMaxLdsProbe
@@ -159,6 +159,7 @@ __device__ __forceinline__ bool spill_add_window(int32_t *keys, double *vals, in
     const uint32_t hk = (uint32_t)key * 0x85EBCA6Bu;
     const uint32_t wmask = mask < kSpillWindow - 1u ? mask : kSpillWindow - 1u;
     uint32_t h = hk & wmask;
+#pragma unroll 1
     for (int p = 0; p < 16; ++p) {
         if (spill_try(keys, vals, used, used_cnt, h, key, w)) return true;
         h = (h + 1) & wmask;
