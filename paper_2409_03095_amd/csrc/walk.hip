@@ -23,10 +23,12 @@
 //  * the rows of a wave start together and are finalized one after the other;
 //  * at the end of the row the wave filters the slots with a ballot, compacts the
 //    survivors in place, scales them by 1 / d_c, sorts them by column with a
-//    bitonic network in LDS and appends them to an output pool.
+//    bitonic network (in registers up to 256 of them, else in LDS) and appends them
+//    to an output pool.
 #include "common.hpp"
 #include "walk_args.hpp"
 #include "walk_common.hpp"
+#include "wave_sort.hpp"
 
 namespace mcmi {
 
@@ -50,6 +52,13 @@ __device__ __forceinline__ void exch(uint64_t &a, uint64_t &b, bool up) {
     b = up ? hi : lo;
 }
 
+// lane 0's value as a wave-uniform one
+__device__ __forceinline__ int64_t first_lane(int64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 __device__ __forceinline__ int64_t next_task(const WalkArgs &a, int &queue, int64_t &lo, int64_t &hi) {
     if (lo < hi) return lo++;
     const int lane = lane_id();
@@ -69,9 +78,9 @@ __device__ __forceinline__ int64_t next_task(const WalkArgs &a, int &queue, int6
             }
         }
     }
-    clo = __shfl(clo, 0, 64);
-    chi = __shfl(chi, 0, 64);
-    queue = __shfl(queue, 0, 64);
+    clo = first_lane(clo);
+    chi = first_lane(chi);
+    queue = __builtin_amdgcn_readfirstlane(queue);
     if (clo < 0) return -1;
     lo = clo + 1;
     hi = chi;
@@ -194,6 +203,64 @@ __device__ __forceinline__ void chain_step(const WalkArgs &a, ChainSt &ch, int s
     }
 }
 
+// Sorts the row's K <= 64 W survivors (keys tk, sums tv) by key into ps (positions in
+// the low 8 bits) and turns keys and sums, in place, into columns and M_rc. False,
+// with the survivors as they were, when the keys span 2^24 or more.
+template <bool kCmp, int W>
+__device__ __forceinline__ bool finish_sorted(const WalkArgs &a, int32_t *tk, double *tv, uint32_t *ps, int K,
+                                              double nd, double ninv, bool pow2) {
+    const int lane = lane_id();
+    int32_t key[W];
+    uint32_t mn = ~0u, mx = 0u;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const int i = lane * W + q;
+        key[q] = i < K ? tk[i] : 0;
+    }
+    int32_t rw[W];
+    double d[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        rw[q] = key[q];
+        d[q] = 1.0;
+        if (lane * W + q < K) {
+            if (kCmp) {
+                const uint32_t *h = a.rec32 + (size_t)(uint32_t)key[q] * kUnitWords32;
+                rw[q] = (int32_t)h[0];
+                d[q] = *(const double *)(h + 6);
+            } else {
+                d[q] = a.diag[key[q]];
+            }
+            mn = min(mn, (uint32_t)key[q]);
+            mx = max(mx, (uint32_t)key[q]);
+        }
+    }
+    mn = wavesort::wave_extreme<false>(mn);
+    mx = wavesort::wave_extreme<true>(mx);
+    if (mx - mn >= (1u << 24)) return false;
+    uint32_t e[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const int i = lane * W + q;
+        e[q] = i < K ? (((uint32_t)key[q] - mn) << 8) | (uint32_t)i : ~0u;
+    }
+    wavesort::sort_words<W>(e, lane);
+#pragma unroll
+    for (int q = 0; q < W; ++q) ps[lane * W + q] = e[q];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const int i = lane * W + q;
+        if (i < K) {
+            const double acc = tv[i];
+            const double nhat = pow2 ? acc * ninv : acc / nd;
+            tk[i] = rw[q];
+            tv[i] = nhat / d[q];
+        }
+    }
+    wave_sync();
+    return true;
+}
+
 // The 64 / kG rows of one wave (one per group of kG lanes; cur and nxt hold each
 // lane's own group's row); each lane keeps kC of its row's chains in flight.
 template <bool kF32, int kG, int kC, bool kCmp>
@@ -248,16 +315,24 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
     unsigned long long trans = 0, spilled = 0;
     bool spill_full = false;
 
-    while (true) {
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < kC; ++k) any |= ch[k].active;
-        if (!__any(any)) break;
-#pragma unroll
-        for (int k = 0; k < kC; ++k)
-            if (ch[k].active)
-                chain_step<kF32, kCmp>(a, ch[k], kG * kC, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, hmask, hshift,
-                                 gskeys, gsvals, gsused, spill_cnt + grp, smask, trans, spilled, spill_full);
+    if constexpr (kC == 1) {
+        // one chain per lane: a lane leaves the loop with its last chain (1024^2 grid with
+        // per-row chains 7.9 -> 7.5 ms, 33 x 31 grid 150 -> 140 us against a wave vote per step)
+        while (ch[0].active)
+            chain_step<kF32, kCmp>(a, ch[0], kG, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, hmask, hshift, gskeys,
+                                   gsvals, gsused, spill_cnt + grp, smask, trans, spilled, spill_full);
+    } else {
+        while (true) {
+            bool any = false;
+    #pragma unroll
+            for (int k = 0; k < kC; ++k) any |= ch[k].active;
+            if (!__any(any)) break;
+    #pragma unroll
+            for (int k = 0; k < kC; ++k)
+                if (ch[k].active)
+                    chain_step<kF32, kCmp>(a, ch[k], kG * kC, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, hmask, hshift,
+                                     gskeys, gsvals, gsused, spill_cnt + grp, smask, trans, spilled, spill_full);
+        }
     }
     wave_sync();
     // the next rows' ids and record offsets load now, their headers during the
@@ -301,24 +376,44 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
                 a.filter_m ? fabs(nhat / (kCmp ? diag_of_c(a.rec32, (uint32_t)key) : a.diag[key])) : fabs(nhat);
             return nhat != 0.0 && test >= a.eps;
         };
+        // Four consecutive slots per lane and round (16-byte LDS reads); the survivors
+        // move to the front of the table in any order, they are sorted below. A round
+        // writes only slots that it or an earlier round has read.
+        const double hi_t = exact ? __builtin_huge_val() : hi, lo_t = exact ? 0.0 : lo;
         int K = 0;
-        for (int base = 0; base < Hg; base += 64) {
-            const int s = base + lane;
-            int32_t key = kEmpty;
-            double acc = 0.0;
+        for (int base = 0; base < Hg; base += 256) {
+            const int s = base + 4 * lane;
+            i32x4v kk = {kEmpty, kEmpty, kEmpty, kEmpty};
+            f64x2v va = {0.0, 0.0}, vb = {0.0, 0.0};
             if (s < Hg) {
-                key = tk[s];
-                acc = tv[s];
+                kk = *(const i32x4v *)(tk + s);
+                va = *(const f64x2v *)(tv + s);
+                vb = *(const f64x2v *)(tv + s + 2);
             }
-            const bool keep = key != kEmpty && keep_test(key, acc);
-            const uint64_t km = ballot(keep);
+            const int32_t key4[4] = {kk.x, kk.y, kk.z, kk.w};
+            const double acc4[4] = {va.x, va.y, vb.x, vb.y};
+            bool keep[4], near = false;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double aa = fabs(acc4[q]);
+                keep[q] = key4[q] >= 0 && (aa > hi_t || key4[q] == kg);
+                near |= key4[q] >= 0 && !keep[q] && aa >= lo_t;
+            }
+            if (__any(near)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) keep[q] = key4[q] >= 0 && keep_test(key4[q], acc4[q]);
+            }
             wave_sync();
-            if (keep) {
-                const int pos = K + mask_rank(km);
-                tk[pos] = key;
-                tv[pos] = acc;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t km = ballot(keep[q]);
+                if (keep[q]) {
+                    const int pos = K + mask_rank(km);
+                    tk[pos] = key4[q];
+                    tv[pos] = acc4[q];
+                }
+                K += __popcll(km);
             }
-            K += __popcll(km);
         }
         wave_sync();
         if (!hdr_issued) {
@@ -358,31 +453,30 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         // header unit, loaded together), N_rc = acc / N, and without top-k at once
         // M_rc = N_rc / d_c; four entries per lane in flight
         const bool scale_now = a.topk <= 0;
-        // Compact records: record offsets order like the rows they start, so the
-        // survivors (up to 256, no top-k) are sorted by their keys while the loads
-        // of their rows and d_c are in flight; the rows and M_rc = (acc / N) / d_c
-        // replace the keys and sums after the sort.
-        int PS0 = 1;
-        while (PS0 < K) PS0 <<= 1;
-        const bool early = kCmp && scale_now && K <= 256 && K + PS0 <= Hg;
-        int32_t erw[4];
-        double ed[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            erw[q] = 0;
-            ed[q] = 1.0;
-        }
+        // Up to 256 survivors without top-k: their keys (record offsets order like the
+        // rows they start) are sorted in registers while the loads of their rows and
+        // d_c are in flight; M_rc = (acc / N) / d_c and the columns then replace the
+        // sums and keys in place and go out in the sorted order. A sorted word is
+        // (key - smallest key) << 8 | position, so the keys must span less than 2^24
+        // (on the 160^3 27-point matrix they span up to 9.7e6 units; rows that span more
+        // take the general path below). With the 64-bit network in LDS (about 20 round
+        // trips), one slot per lane and read in the filter, and two wave sums per row,
+        // the walks took 55.3 ms (160^3), 23.3 ms (batched, 128 chains), 9.0 ms (77^3
+        // binary64) and 9.4 ms (1024^2 grid, 1-96 chains) against 51.4, 21.6, 8.2 and 7.8.
+        const int W = K <= 64 ? 1 : K <= 128 ? 2 : 4;
+        uint32_t *ps = (uint32_t *)(tv + (Hg - 32 * W));
+        bool early = scale_now && K <= 256 && K + 32 * W <= Hg;
         if (early) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = lane + 64 * q;
-                if (i < K) {
-                    const uint32_t *h = a.rec32 + (size_t)(uint32_t)tk[i] * kUnitWords32;
-                    erw[q] = (int32_t)h[0];
-                    ed[q] = *(const double *)(h + 6);
-                }
-            }
-        } else {
+            const double ninv = 1.0 / nd;
+            const bool pow2 = (Ng & (Ng - 1)) == 0;  // acc / N = acc (1 / N) exactly
+            if (W == 1)
+                early = finish_sorted<kCmp, 1>(a, tk, tv, ps, K, nd, ninv, pow2);
+            else if (W == 2)
+                early = finish_sorted<kCmp, 2>(a, tk, tv, ps, K, nd, ninv, pow2);
+            else
+                early = finish_sorted<kCmp, 4>(a, tk, tv, ps, K, nd, ninv, pow2);
+        }
+        if (!early) {
             for (int i0 = lane; i0 < K; i0 += 256) {
                 int32_t rw[4];
                 double d[4];
@@ -452,8 +546,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
             }
         }
 
-        // Bitonic sort by column (on the early path by record offset, which orders
-        // the same way). A pass has PS / 2 compare-exchange pairs, pair p
+        // Bitonic sort by column in LDS. A pass has PS / 2 compare-exchange pairs, pair p
         // joining i (p with a zero bit inserted at jj) and i | jj, so every lane has a
         // pair. When the value slots past the survivors have room, the sort moves
         // one word per entry, (column << 13) | position, in that free part of the
@@ -463,7 +556,8 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         while (PS < K) PS <<= 1;
         const bool packed = K + PS <= Hg;
         uint64_t *pk = (uint64_t *)(tv + (Hg - PS));
-        if (packed) {
+        if (early) {
+        } else if (packed) {
             for (int s = lane; s < PS; s += 64) pk[s] = s < K ? ((uint64_t)(uint32_t)tk[s] << 13) | (uint64_t)s : ~0ull;
             wave_sync();
             for (int k = 2; k <= PS; k <<= 1) {
@@ -523,19 +617,6 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
             }
         }
 
-        if (early) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = lane + 64 * q;
-                if (i < K) {
-                    const double nhat = tv[i] / nd;
-                    tk[i] = erw[q];
-                    tv[i] = nhat / ed[q];
-                }
-            }
-            wave_sync();
-        }
-
         // append to the pool unless a table overflowed for this row (then it is rerun)
         const bool row_spill_full = __any(spill_full && grp == g);
         const bool row_stage_full = __any(stage_full);
@@ -559,7 +640,11 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         const bool ok = fits && !row_spill_full && !row_stage_full;
         if (ok) {
             for (int i = lane; i < K; i += 64) {
-                if (packed) {
+                if (early) {
+                    const uint32_t e = ps[i] & 255u;
+                    a.pool_col[pos0 + i] = tk[e];
+                    a.pool_val[pos0 + i] = tv[e];
+                } else if (packed) {
                     const uint64_t e = pk[i];
                     a.pool_col[pos0 + i] = tk[e & 8191u];
                     a.pool_val[pos0 + i] = tv[e & 8191u];
@@ -569,8 +654,11 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
                 }
             }
         }
-        const unsigned long long tg = wave_sum(grp == g ? trans : 0ull);
-        const unsigned long long sg = wave_sum(grp == g ? spilled : 0ull);
+        // statistics per lane, summed over the wave when the kernel ends
+        if (grp == g) {
+            if (ok) wstats[0] += trans;
+            wstats[1] += spilled;
+        }
         if (lane == 0) {
             a.row_start[slot] = ok ? ((int64_t)pos0 | a.pool_tag) : -1;
             a.row_cnt[slot] = (uint32_t)K;
@@ -579,18 +667,12 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
             if (row_spill_full) f |= kFlagSpill;
             if (row_stage_full) f |= kFlagStage;
             if (f) atomicOr(a.flags, f);
-            if (ok) {
-                wstats[0] += tg;
-                wstats[2] += (unsigned long long)Ng;
-            }
-            wstats[1] += sg;
+            if (ok) wstats[2] += (unsigned long long)Ng;
         }
         // clear this row's table for the next row of its group
         wave_sync();
-        for (int s = lane; s < Hg; s += 64) {
-            tk[s] = kEmpty;
-            tv[s] = 0.0;
-        }
+        for (int s = 4 * lane; s < Hg; s += 256) *(i32x4v *)(tk + s) = i32x4v{kEmpty, kEmpty, kEmpty, kEmpty};
+        for (int s = 2 * lane; s < Hg; s += 128) *(f64x2v *)(tv + s) = f64x2v{0.0, 0.0};
         if (lane == 0) spill_cnt[g] = 0;
         wave_sync();
     }
@@ -598,7 +680,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
 }
 
 template <bool kF32, int kG, int kC, bool kCmp>
-__global__ void __launch_bounds__(256) k_walk(WalkArgs a) {
+__global__ void __launch_bounds__(256, 3) k_walk(WalkArgs a) {
     constexpr int P = 64 / kG;
     extern __shared__ __align__(16) unsigned char smem[];
     const int waves = blockDim.x >> 6;
@@ -641,6 +723,8 @@ __global__ void __launch_bounds__(256) k_walk(WalkArgs a) {
         cur = nxt;
     }
     // statistics: one set of atomics per wave
+    wstats[0] = wave_sum(wstats[0]);
+    wstats[1] = wave_sum(wstats[1]);
     if (lane == 0) {
         if (wstats[0]) atomicAdd(&a.stats[0], wstats[0]);
         if (wstats[1]) atomicAdd(&a.stats[1], wstats[1]);

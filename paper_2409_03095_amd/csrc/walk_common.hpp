@@ -33,6 +33,7 @@ __device__ __forceinline__ void read_bucket(const int32_t *keys, uint32_t b, int
 // probe that finds the bucket taken by another lane's compare-and-swap reads it
 // again).
 typedef int i32x4v __attribute__((ext_vector_type(4)));
+typedef double f64x2v __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void read_bucket_wave(const int32_t *keys, uint32_t b, int32_t k[4]) {
     const i32x4v q = *(const i32x4v *)(keys + b);
     k[0] = q.x;
