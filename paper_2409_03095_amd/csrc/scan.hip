@@ -291,7 +291,8 @@ hipError_t expand_blocks(int64_t nblocks, const int32_t *start, const int32_t *c
 template <int G, int U>
 __global__ void __launch_bounds__(256) k_spmv(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                                               const double *__restrict__ v, const double *__restrict__ x,
-                                              double *__restrict__ y) {
+                                              double *__restrict__ y, const int32_t *__restrict__ stop) {
+    if (stop && *stop != 0) return;  // an iteration queued past the end of its solve
     const int sub = threadIdx.x & (G - 1);
     const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / G;
     int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
@@ -333,24 +334,24 @@ __global__ void __launch_bounds__(256) k_spmv(int64_t n, const int64_t *__restri
 
 template <int G, int U>
 hipError_t launch_spmv(int64_t n, const int64_t *rp, const int32_t *ci, const double *v, const double *x, double *y,
-                       hipStream_t s) {
+                       const int32_t *stop, hipStream_t s) {
     int64_t blocks = (n * G + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    k_spmv<G, U><<<(unsigned)blocks, 256, 0, s>>>(n, rp, ci, v, x, y);
+    k_spmv<G, U><<<(unsigned)blocks, 256, 0, s>>>(n, rp, ci, v, x, y, stop);
     return hipGetLastError();
 }
 
 hipError_t spmv(int64_t n, int64_t nnz, const int64_t *rp, const int32_t *ci, const double *v, const double *x,
-                double *y, hipStream_t s) {
+                double *y, const int32_t *stop, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const double per_row = (double)nnz / (double)n;
-    if (per_row < 12.0) return launch_spmv<8, 4>(n, rp, ci, v, x, y, s);
-    if (per_row < 24.0) return launch_spmv<16, 4>(n, rp, ci, v, x, y, s);
-    if (per_row < 96.0) return launch_spmv<32, 4>(n, rp, ci, v, x, y, s);
+    if (per_row < 12.0) return launch_spmv<8, 4>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 24.0) return launch_spmv<16, 4>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 96.0) return launch_spmv<32, 4>(n, rp, ci, v, x, y, stop, s);
     // rows of 96-191 entries (the 160^3 27-point M: 165): 16 lanes per row with
     // twelve entries each in flight measured 2.07 vs 2.43 ms for 32 x 6
-    if (per_row < 192.0) return launch_spmv<16, 12>(n, rp, ci, v, x, y, s);
-    return launch_spmv<64, 4>(n, rp, ci, v, x, y, s);
+    if (per_row < 192.0) return launch_spmv<16, 12>(n, rp, ci, v, x, y, stop, s);
+    return launch_spmv<64, 4>(n, rp, ci, v, x, y, stop, s);
 }
 
 }  // namespace mcmi
