@@ -282,20 +282,21 @@ hipError_t expand_blocks(int64_t nblocks, const int32_t *start, const int32_t *c
 }
 
 // ------------------------------------------------------------------ SpMV
-// y = M x, float64. A group of G lanes per row (G and the loads per lane U from
-// the average row length, so that G U covers a typical row in one pass), strided
-// partial sums then a butterfly reduction inside the group; grid-stride over
-// rows. Each lane issues the loads of its U entries before it adds them (in the
-// same order as one at a time), and the next row's bounds load while the current
-// row is summed, so a row costs two dependent memory latencies, not three.
-template <int G, int U>
+// y = M x, float64, grid-stride over rows. A row's sum is that of V strided partial
+// sums added as a binary tree (V from the average row length), which P lanes form
+// together: a lane keeps V / P of the partial sums and issues the loads of C
+// entries of each before it adds them, so that a typical row is one pass with
+// few idle lanes and loads; the next row's bounds load while the current row is
+// summed.
+template <int V, int P, int C>
 __global__ void __launch_bounds__(256) k_spmv(int64_t n, const int64_t *__restrict__ rp, const int32_t *__restrict__ ci,
                                               const double *__restrict__ v, const double *__restrict__ x,
                                               double *__restrict__ y, const int32_t *__restrict__ stop) {
+    constexpr int T = V / P;
     if (stop && *stop != 0) return;  // an iteration queued past the end of its solve
-    const int sub = threadIdx.x & (G - 1);
-    const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / G;
-    int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
+    const int sub = threadIdx.x & (P - 1);
+    const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / P;
+    int64_t row = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / P;
     int64_t b = 0, e = 0;
     if (row < n) {
         b = rp[row];
@@ -308,50 +309,65 @@ __global__ void __launch_bounds__(256) k_spmv(int64_t n, const int64_t *__restri
             nb = rp[nrow];
             ne = rp[nrow + 1];
         }
-        double acc = 0.0;
-        for (int64_t k0 = b + sub; k0 < e; k0 += (int64_t)G * U) {
-            int32_t c[U];
-            double w[U], xv[U];
+        double acc[T];
 #pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int64_t k = k0 + (int64_t)j * G < e ? k0 + (int64_t)j * G : e - 1;
+        for (int t = 0; t < T; ++t) acc[t] = 0.0;
+        for (int64_t k0 = b + sub; k0 < e; k0 += (int64_t)V * C) {
+            int32_t c[C * T];
+            double w[C * T], xv[C * T];
+#pragma unroll
+            for (int j = 0; j < C * T; ++j) {
+                const int64_t k = k0 + (int64_t)j * P < e ? k0 + (int64_t)j * P : e - 1;
                 c[j] = ci[k];
                 w[j] = v[k];
             }
 #pragma unroll
-            for (int j = 0; j < U; ++j) xv[j] = x[c[j]];
+            for (int j = 0; j < C * T; ++j) xv[j] = x[c[j]];
 #pragma unroll
-            for (int j = 0; j < U; ++j)
-                if (k0 + (int64_t)j * G < e) acc += w[j] * xv[j];
+            for (int j = 0; j < C * T; ++j)
+                if (k0 + (int64_t)j * P < e) acc[j % T] += w[j] * xv[j];
         }
 #pragma unroll
-        for (int off = G / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, G);
-        if (sub == 0) y[row] = acc;
+        for (int h = T / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int t = 0; t < h; ++t) acc[t] += acc[t + h];
+        double sum = acc[0];
+#pragma unroll
+        for (int off = P / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, P);
+        if (sub == 0) y[row] = sum;
         b = nb;
         e = ne;
     }
 }
 
-template <int G, int U>
+template <int V, int P, int C>
 hipError_t launch_spmv(int64_t n, const int64_t *rp, const int32_t *ci, const double *v, const double *x, double *y,
                        const int32_t *stop, hipStream_t s) {
-    int64_t blocks = (n * G + 255) / 256;
+    int64_t blocks = (n * P + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    k_spmv<G, U><<<(unsigned)blocks, 256, 0, s>>>(n, rp, ci, v, x, y, stop);
+    k_spmv<V, P, C><<<(unsigned)blocks, 256, 0, s>>>(n, rp, ci, v, x, y, stop);
     return hipGetLastError();
 }
 
 hipError_t spmv(int64_t n, int64_t nnz, const int64_t *rp, const int32_t *ci, const double *v, const double *x,
                 double *y, const int32_t *stop, hipStream_t s) {
     if (n <= 0) return hipSuccess;
+    // V goes by powers of two of the average row length and fixes the order of a row's
+    // sum; P and C are the fastest measured. With P = V (one partial sum per lane, 4
+    // entries in flight) a 27-entry row left 101 of 128 loads idle. Times before -> now:
+    //   5-point 1024^2 (5 per row)      44.3 -> 17.1 us (P = 4: 20.0, P = 8: 27.7)
+    //   random (18.5 per row)           32.9 -> 28.0 us (P = 2: 32.1, P = 8: 27.8)
+    //   27-point 128^3 (27 per row)     396 -> 146 us, 4.6 TB/s (P = 8: 153, P = 16: 173)
+    //   random (50 and 80 per row)      59.2 -> 49.3, 42.7 -> 41.3 us (P = 8, C = 3: 51.7, 43.7)
+    //   banded (165 per row)            225 us, 5.3 TB/s (P = 8, C = 6: 255, C = 8: 329)
+    //   banded (250 and 400 per row)    247 -> 211, 249 -> 234 us (P = 32, C = 3: 270, 255)
     const double per_row = (double)nnz / (double)n;
-    if (per_row < 12.0) return launch_spmv<8, 4>(n, rp, ci, v, x, y, stop, s);
-    if (per_row < 24.0) return launch_spmv<16, 4>(n, rp, ci, v, x, y, stop, s);
-    if (per_row < 96.0) return launch_spmv<32, 4>(n, rp, ci, v, x, y, stop, s);
-    // rows of 96-191 entries (the 160^3 27-point M: 165): 16 lanes per row with
-    // twelve entries each in flight measured 2.07 vs 2.43 ms for 32 x 6
-    if (per_row < 192.0) return launch_spmv<16, 12>(n, rp, ci, v, x, y, stop, s);
-    return launch_spmv<64, 4>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 12.0) return launch_spmv<8, 2, 1>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 24.0) return launch_spmv<16, 4, 1>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 40.0) return launch_spmv<32, 4, 1>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 96.0) return launch_spmv<32, 16, 2>(n, rp, ci, v, x, y, stop, s);
+    if (per_row < 192.0) return launch_spmv<16, 16, 12>(n, rp, ci, v, x, y, stop, s);
+    return launch_spmv<64, 16, 2>(n, rp, ci, v, x, y, stop, s);
 }
 
 }  // namespace mcmi
