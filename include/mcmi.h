@@ -310,7 +310,7 @@ mcmi_status mcmi_allocate(const float *pred_dev, const int32_t *cost_dev, int64_
  * hipGraph stream capture, tight serving loops, harnesses that forbid
  * hipMalloc). Same kernels and the same results (chains_dev, lambda, fallback
  * flag) as mcmi_allocate, but every temporary lives in a static device workspace
- * of 256 B + 8 B per row for at most 4,194,304 rows (32 MiB + 256 B, one copy
+ * of 64 KiB + 8 B per row for at most 4,194,304 rows (32 MiB + 64 KiB, one copy
  * per GPU, held until the process ends); n above that limit returns
  * MCMI_ERR_ARG before anything is launched. lambda_dev (double) and fallback_dev
  * (int32) are optional device outputs (NULL: not written). Fully asynchronous:

@@ -551,20 +551,29 @@ extern "C" mcmi_status mcmi_mlp_adam_step(mcmi_mlp *net, const float *grad_dev, 
 // sum_r N_r cost_r is the largest total not above the budget: hi doubles from 1
 // while total(hi) <= budget (and hi < 1e30), then 100 halvings of [0, hi] keep
 // total(lo) <= budget < total(hi); lambda = lo. Every total is an exact integer
-// sum, so the grid-wide evaluation below (one pass over the rows per step, the
-// step's decision taken on the device, no host round trip) makes the same
-// decisions as a sequential loop. Non-finite predictions fall back to the
-// uniform allocation N_r = max(1, floor(budget / sum_r cost_r)).
+// sum. A launch evaluates kCand candidates in one pass over the rows: the next
+// kCand doublings, or every midpoint that the next kDepth halvings can reach; the last
+// workgroup to arrive then takes the same decisions, in the same order, as a
+// sequential loop would, and ends the search once a halving changes nothing. At
+// 1M rows that is about 20 working passes of 23 us instead of 160 passes of 15 us, each
+// with a one-thread launch behind it (allocation 5.2 -> 0.55 ms). Non-finite
+// predictions fall back to the uniform allocation N_r = max(1, floor(budget / sum_r cost_r)).
 namespace mcmi {
 namespace {
 
+constexpr int kDepth = 4, kCand = (1 << kDepth) - 1;
+constexpr int kAllocBlocks = 512;  // most workgroups of a pass
+constexpr int kDoublings = 101;    // hi reaches 2^100 > 1e30
+constexpr int kPasses = (kDoublings + kCand - 1) / kCand + 100 / kDepth;
+
 struct AllocState {
     double lo, hi;
-    long long total;  // of the current candidate
     long long bad;    // non-finite predictions
     long long csum;   // sum of costs
     int32_t phase;    // 0: doubling hi, 1: halving, 2: done
     int32_t halvings;
+    int32_t hi_over;  // total(hi) > budget is known
+    uint32_t arrived;
 };
 
 __device__ __forceinline__ long long block_sum_ll(long long v, long long *red) {
@@ -578,11 +587,11 @@ __device__ __forceinline__ long long block_sum_ll(long long v, long long *red) {
     return t;
 }
 
-__device__ __forceinline__ long long chains_of(double lam, double e) {
+__device__ __forceinline__ int32_t chains_of(double lam, double e) {
     double k = rint(lam * e);
     if (!(k >= 1.0)) k = 1.0;
     if (k > 2147483647.0) k = 2147483647.0;
-    return (long long)k;
+    return (int32_t)k;
 }
 
 __global__ void __launch_bounds__(256) k_alloc_prep(const float *pred, const int32_t *cost, int64_t n, double *e,
@@ -604,37 +613,107 @@ __global__ void __launch_bounds__(256) k_alloc_prep(const float *pred, const int
     }
 }
 
-// total(candidate) into st->total; the candidate is hi while doubling, else the midpoint
-__global__ void __launch_bounds__(256) k_alloc_total(const double *e, const int32_t *cost, int64_t n,
-                                                     AllocState *st) {
-    __shared__ long long red[4];
+// One pass: the totals of this state's candidates (workgroup sums in part, kCand per
+// workgroup), then the last workgroup's decisions.
+__global__ void __launch_bounds__(256) k_alloc_pass(const double *__restrict__ e, const int32_t *__restrict__ cost,
+                                                    int64_t n, long long budget, long long *part, AllocState *st) {
+    __shared__ long long red[kCand][4];
+    __shared__ int last;
     const int32_t phase = st->phase;
     if (phase == 2) return;
-    const double lam = phase == 0 ? st->hi : 0.5 * (st->lo + st->hi);
-    long long t = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += stride)
-        t += chains_of(lam, e[r]) * (long long)cost[r];
-    t = block_sum_ll(t, red);
-    if (threadIdx.x == 0) atomicAdd((unsigned long long *)&st->total, (unsigned long long)t);
-}
-
-// the step's decision (one thread)
-__global__ void k_alloc_update(AllocState *st, long long budget) {
-    if (st->phase == 0) {
-        if (st->total <= budget && st->hi < 1e30)
-            st->hi *= 2.0;
-        else
-            st->phase = 1;
-    } else if (st->phase == 1) {
-        const double mid = 0.5 * (st->lo + st->hi);
-        if (st->total <= budget)
-            st->lo = mid;
-        else
-            st->hi = mid;
-        if (++st->halvings == 100) st->phase = 2;
+    // candidates: hi, 2 hi, 4 hi, ..; or the midpoints as a tree (children of node i: 2 i + 1
+    // after hi = mid, 2 i + 2 after lo = mid)
+    double lo[kCand], hi[kCand], lam[kCand];
+    lo[0] = st->lo;
+    hi[0] = st->hi;
+    if (phase == 0) {
+        lam[0] = hi[0];
+#pragma unroll
+        for (int i = 1; i < kCand; ++i) lam[i] = lam[i - 1] * 2.0;
+    } else {
+#pragma unroll
+        for (int i = 0; i < kCand; ++i) {
+            if (i > 0) {
+                const int up = (i - 1) / 2;
+                lo[i] = (i & 1) ? lo[up] : lam[up];
+                hi[i] = (i & 1) ? lam[up] : hi[up];
+            }
+            lam[i] = 0.5 * (lo[i] + hi[i]);
+        }
     }
-    st->total = 0;
+    long long sum[kCand];
+#pragma unroll
+    for (int i = 0; i < kCand; ++i) sum[i] = 0;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += stride) {
+        const double er = e[r];
+        const int32_t c = cost[r];
+#pragma unroll
+        for (int i = 0; i < kCand; ++i) sum[i] += (long long)chains_of(lam[i], er) * (long long)c;
+    }
+    const int t = threadIdx.x, w = t >> 6;
+#pragma unroll
+    for (int i = 0; i < kCand; ++i) {
+        const long long v = wave_sum(sum[i]);
+        if ((t & 63) == 0) red[i][w] = v;
+    }
+    __syncthreads();
+    if (t < kCand)
+        __hip_atomic_store(part + (size_t)blockIdx.x * kCand + t, red[t][0] + red[t][1] + red[t][2] + red[t][3],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (t == 0)
+        last = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
+    __syncthreads();
+    if (!last) return;
+#pragma unroll
+    for (int i = 0; i < kCand; ++i) {
+        long long v = 0;
+        for (int b = t; b < (int)gridDim.x; b += 256)
+            v += __hip_atomic_load(part + (size_t)b * kCand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = wave_sum(v);
+        if ((t & 63) == 0) red[i][w] = v;
+    }
+    __syncthreads();
+    if (t != 0) return;
+    st->arrived = 0u;
+    auto total = [&](int i) { return red[i][0] + red[i][1] + red[i][2] + red[i][3]; };
+    if (phase == 0) {
+        double h = st->hi;
+        for (int i = 0; i < kCand; ++i) {
+            const bool fits = total(i) <= budget;
+            if (fits && h < 1e30) {
+                h *= 2.0;
+            } else {
+                st->hi_over = !fits;
+                st->phase = 1;
+                break;
+            }
+        }
+        st->hi = h;
+        return;
+    }
+    double l = st->lo, h = st->hi;
+    int32_t over = st->hi_over, done = st->halvings, node = 0;
+    bool settled = false;
+    for (int d = 0; d < kDepth && done < 100 && !settled; ++d, ++done) {
+        const double mid = 0.5 * (l + h);
+        // a midpoint that equals an end whose side is known changes nothing from here on
+        settled = (mid == l && l > 0.0) || (mid == h && over);
+        if (total(node) <= budget) {
+            l = mid;
+            node = 2 * node + 2;
+        } else {
+            h = mid;
+            over = 1;
+            node = 2 * node + 1;
+        }
+    }
+    st->lo = l;
+    st->hi = h;
+    st->hi_over = over;
+    st->halvings = done;
+    if (done == 100 || settled) st->phase = 2;
 }
 
 __global__ void __launch_bounds__(256) k_alloc_write(const double *e, int64_t n, long long budget,
@@ -660,20 +739,37 @@ __global__ void k_alloc_init(AllocState *st) {
     if (threadIdx.x == 0) {
         st->lo = 0.0;
         st->hi = 1.0;
-        st->total = 0;
         st->bad = 0;
         st->csum = 0;
         st->phase = 0;
         st->halvings = 0;
+        st->hi_over = 0;
+        st->arrived = 0u;
     }
 }
 
 // Workspace of mcmi_allocate_noalloc: the bisection state, the lambda and
-// fallback slots, then exp(pred_r) for up to kNoAllocMaxRows rows.
+// fallback slots, a pass's workgroup sums, then exp(pred_r) for up to kNoAllocMaxRows rows.
 constexpr int64_t kNoAllocMaxRows = int64_t(1) << 22;
-constexpr size_t kNoAllocHead = 256;
+constexpr size_t kNoAllocPart = 256;
+constexpr size_t kNoAllocHead = 65536;
+static_assert(kNoAllocPart + (size_t)kAllocBlocks * kCand * sizeof(long long) <= kNoAllocHead, "workgroup sums");
 constexpr size_t kNoAllocBytes = kNoAllocHead + (size_t)kNoAllocMaxRows * sizeof(double);
 static_assert(sizeof(AllocState) <= 64, "state slot");
+
+unsigned alloc_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 256, kAllocBlocks); }
+
+// The whole search on `s`: st, part (kAllocBlocks x kCand), e (n) and the outputs on the device.
+hipError_t launch_allocation(const float *pred, const int32_t *cost, int64_t n, int64_t budget, AllocState *st,
+                             long long *part, double *e, int32_t *chains, double *lam, int32_t *fbk, hipStream_t s) {
+    const unsigned blocks = alloc_grid(n);
+    k_alloc_init<<<1, 64, 0, s>>>(st);
+    k_alloc_prep<<<blocks, 256, 0, s>>>(pred, cost, n, e, st);
+    for (int it = 0; it < kPasses; ++it)  // passes after the search has ended return at once
+        k_alloc_pass<<<blocks, 256, 0, s>>>(e, cost, n, (long long)budget, part, st);
+    k_alloc_write<<<blocks, 256, 0, s>>>(e, n, (long long)budget, st, chains, lam, fbk);
+    return hipGetLastError();
+}
 
 }  // namespace
 }  // namespace mcmi
@@ -713,39 +809,26 @@ extern "C" mcmi_status mcmi_allocate(const float *pred_dev, const int32_t *cost_
     if (!pred_dev || !cost_dev || !chains_dev || n < 1 || budget < 1)
         return fail(MCMI_ERR_ARG, "mcmi_allocate: bad argument");
     hipStream_t s = (hipStream_t)stream;
-    double *e = nullptr, *lam = nullptr;
-    int32_t *fbk = nullptr;
-    AllocState *st = nullptr;
+    // exp(pred), then the state, lambda, fallback flag and workgroup sums
+    double *e = nullptr;
+    unsigned char *head = nullptr;
     MCMI_HIP(dev_alloc((void **)&e, (size_t)n * sizeof(double), s));
-    MCMI_HIP(dev_alloc((void **)&lam, sizeof(double) + sizeof(int32_t) * 2 + sizeof(AllocState), s));
-    fbk = (int32_t *)(lam + 1);
-    st = (AllocState *)(fbk + 2);
-    const AllocState init{0.0, 1.0, 0, 0, 0, 0, 0};
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    hipError_t err = hipMemcpyAsync(st, &init, sizeof(init), hipMemcpyHostToDevice, s);
-    if (err == hipSuccess) {
-        k_alloc_prep<<<(unsigned)blocks, 256, 0, s>>>(pred_dev, cost_dev, n, e, st);
-        err = hipGetLastError();
+    hipError_t err = dev_alloc((void **)&head, kNoAllocHead, s);
+    if (err != hipSuccess) {
+        dev_release(e, s);
+        return fail(MCMI_ERR_HIP, std::string("mcmi_allocate: ") + hipGetErrorString(err));
     }
-    // at most 101 doublings (hi reaches 2^100 > 1e30) and exactly 100 halvings;
-    // steps after the search has ended return at once
-    for (int it = 0; err == hipSuccess && it < 201; ++it) {
-        k_alloc_total<<<(unsigned)blocks, 256, 0, s>>>(e, cost_dev, n, st);
-        k_alloc_update<<<1, 1, 0, s>>>(st, (long long)budget);
-        err = hipGetLastError();
-    }
-    if (err == hipSuccess) {
-        k_alloc_write<<<(unsigned)blocks, 256, 0, s>>>(e, n, (long long)budget, st, chains_dev, lam, fbk);
-        err = hipGetLastError();
-    }
+    double *lam = (double *)(head + 64);
+    int32_t *fbk = (int32_t *)(head + 72);
+    err = launch_allocation(pred_dev, cost_dev, n, budget, (AllocState *)head, (long long *)(head + kNoAllocPart), e,
+                            chains_dev, lam, fbk, s);
     double hl = 0.0;
     int32_t hf = 0;
     if (err == hipSuccess) err = hipMemcpyAsync(&hl, lam, sizeof(double), hipMemcpyDeviceToHost, s);
     if (err == hipSuccess) err = hipMemcpyAsync(&hf, fbk, sizeof(int32_t), hipMemcpyDeviceToHost, s);
     if (err == hipSuccess) err = hipStreamSynchronize(s);
     dev_release(e, s);
-    dev_release(lam, s);
+    dev_release(head, s);
     if (err != hipSuccess) return fail(MCMI_ERR_HIP, std::string("mcmi_allocate: ") + hipGetErrorString(err));
     if (lambda_host) *lambda_host = hl;
     if (fallback_host) *fallback_host = hf;
@@ -768,21 +851,10 @@ extern "C" mcmi_status mcmi_allocate_noalloc(const float *pred_dev, const int32_
         return fail(MCMI_ERR_HIP, std::string("mcmi_allocate_noalloc: workspace address: ") + hipGetErrorString(err));
     hipStream_t s = (hipStream_t)stream;
     unsigned char *head = (unsigned char *)base;
-    AllocState *st = (AllocState *)head;
-    double *lam = (double *)(head + 64);
-    int32_t *fbk = (int32_t *)(head + 72);
-    double *e = (double *)(head + kNoAllocHead);
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    k_alloc_init<<<1, 64, 0, s>>>(st);
-    k_alloc_prep<<<(unsigned)blocks, 256, 0, s>>>(pred_dev, cost_dev, n, e, st);
-    for (int it = 0; it < 201; ++it) {
-        k_alloc_total<<<(unsigned)blocks, 256, 0, s>>>(e, cost_dev, n, st);
-        k_alloc_update<<<1, 1, 0, s>>>(st, (long long)budget);
-    }
-    k_alloc_write<<<(unsigned)blocks, 256, 0, s>>>(e, n, (long long)budget, st, chains_dev,
-                                                   lambda_dev ? lambda_dev : lam, fallback_dev ? fallback_dev : fbk);
-    err = hipGetLastError();
+    err = launch_allocation(pred_dev, cost_dev, n, budget, (AllocState *)head, (long long *)(head + kNoAllocPart),
+                            (double *)(head + kNoAllocHead), chains_dev,
+                            lambda_dev ? lambda_dev : (double *)(head + 64),
+                            fallback_dev ? fallback_dev : (int32_t *)(head + 72), s);
     if (err != hipSuccess) return fail(MCMI_ERR_HIP, std::string("mcmi_allocate_noalloc: ") + hipGetErrorString(err));
     return MCMI_OK;
 }
