@@ -27,47 +27,75 @@ namespace {
 
 using namespace walkdev;
 
-__global__ void __launch_bounds__(256) k_features(int64_t n, const uint32_t *__restrict__ rec,
+// P lanes per row (several rows share a wavefront), from the compact records: an
+// entry's weight, target and the target's m from its bucket, Shat64 from the
+// target's header. The sums are those of 64 strided partial sums per row added as a
+// binary tree, of which a lane keeps 64 / P. On the 1024^2 5-point grid 0.70 ms with a
+// wavefront per row on the full records, whose build (0.22 ms there, 4.9 ms on the
+// 160^3 matrix) this does without, against 0.11 ms.
+template <int P>
+__global__ void __launch_bounds__(256) k_features(int64_t n, const uint32_t *__restrict__ rec32,
                                                   const uint32_t *__restrict__ roff, double delta, int lmax,
                                                   float *__restrict__ feat) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t r = wave; r < n; r += nwaves) {
-        const uint32_t *recp = rec + (size_t)roff[r] * kUnitWords;
-        const uint32_t m = recp[1], W = recp[2];
-        const double S = __hiloint2double((int)recp[5], (int)recp[4]);
-        double ps = 0.0, pm = 0.0, sgn = 0.0, smax = 0.0;
+    constexpr int T = 64 / P;
+    const int sub = threadIdx.x & (P - 1);
+    const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / P;
+    const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / P;
+    for (int64_t r = group; r < n; r += groups) {
+        const uint32_t *recp = rec32 + (size_t)roff[r] * kUnitWords32;
+        const uint4 h = *(const uint4 *)recp;  // row, m, W, Shat32
+        const uint32_t m = h.y, W = h.z;
+        const double S = *(const double *)(recp + 4);
+        double ps[T], pm[T], sgn[T], smax = 0.0;
         uint32_t wmax = 0;
-        for (uint32_t k = lane; k < m; k += 64) {
-            // bucket k: {T, target, alias target, w}, target's header, alias's header, Shat64s
-            const uint4 *e = (const uint4 *)(recp + (size_t)(1u + k) * kUnitWords);
-            const uint4 q0 = e[0], q1 = e[1], q3 = e[3];
-            const uint32_t w = q0.w;
-            const uint32_t tgt = q0.y;
-            const double St = __hiloint2double((int)q3.y, (int)q3.x);
-            const double mt = (double)q1.y;
-            ps += (double)w * St;
-            pm += (double)w * mt;
-            sgn += (tgt & kSignBit) ? -(double)w : (double)w;
-            smax = St > smax ? St : smax;
-            wmax = w > wmax ? w : wmax;
+#pragma unroll
+        for (int t = 0; t < T; ++t) ps[t] = pm[t] = sgn[t] = 0.0;
+        for (uint32_t k0 = 0; k0 < m; k0 += 64) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint32_t k = k0 + (uint32_t)(t * P + sub);
+                if (k < m) {
+                    const uint32_t *e = recp + (size_t)(1u + k) * kUnitWords32;
+                    const uint4 q0 = *(const uint4 *)e;  // T', target, m and Shat32 of the target's row
+                    const uint32_t w = e[4];
+                    const double St = *(const double *)(rec32 + (size_t)(q0.y & ~kSignBit) * kUnitWords32 + 4);
+                    const double mt = (double)q0.z;
+                    ps[t] += (double)w * St;
+                    pm[t] += (double)w * mt;
+                    sgn[t] += (q0.y & kSignBit) ? -(double)w : (double)w;
+                    smax = St > smax ? St : smax;
+                    wmax = w > wmax ? w : wmax;
+                }
+            }
         }
-        ps = wave_sum(ps);
-        pm = wave_sum(pm);
-        sgn = wave_sum(sgn);
-        smax = wave_max(smax);
-        wmax = wave_max(wmax);
-        if (lane == 0) {
-            float *f = feat + 8 * r;
+#pragma unroll
+        for (int hh = T / 2; hh > 0; hh >>= 1)
+#pragma unroll
+            for (int t = 0; t < hh; ++t) {
+                ps[t] += ps[t + hh];
+                pm[t] += pm[t + hh];
+                sgn[t] += sgn[t + hh];
+            }
+#pragma unroll
+        for (int off = P / 2; off > 0; off >>= 1) {
+            ps[0] += __shfl_xor(ps[0], off, P);
+            pm[0] += __shfl_xor(pm[0], off, P);
+            sgn[0] += __shfl_xor(sgn[0], off, P);
+            const double so = __shfl_xor(smax, off, P);
+            smax = so > smax ? so : smax;
+            const uint32_t wo = (uint32_t)__shfl_xor((int)wmax, off, P);
+            wmax = wo > wmax ? wo : wmax;
+        }
+        if (sub == 0) {
             const double Wd = (double)W;
-            f[0] = (float)log((double)(m > 1u ? m : 1u));
-            f[1] = (float)S;
-            f[2] = m ? (float)(S * (double)wmax / Wd) : 0.f;
-            f[3] = m ? (float)(ps / Wd) : 0.f;
-            f[4] = (float)smax;
-            f[5] = m ? (float)(pm / Wd) : 0.f;
-            f[6] = (m && S > 0.0) ? (float)(fabs(sgn) / Wd) : 0.f;
+            float4 f0, f1;
+            f0.x = (float)log((double)(m > 1u ? m : 1u));
+            f0.y = (float)S;
+            f0.z = m ? (float)(S * (double)wmax / Wd) : 0.f;
+            f0.w = m ? (float)(ps[0] / Wd) : 0.f;
+            f1.x = (float)smax;
+            f1.y = m ? (float)(pm[0] / Wd) : 0.f;
+            f1.z = (m && S > 0.0) ? (float)(fabs(sgn[0]) / Wd) : 0.f;
             double f7;
             if (S > 0.0 && S < 1.0 && delta > 0.0) {
                 const double l = log(delta) / log(S);
@@ -75,7 +103,16 @@ __global__ void __launch_bounds__(256) k_features(int64_t n, const uint32_t *__r
             } else {
                 f7 = S > 0.0 ? (double)lmax : 0.0;
             }
-            f[7] = (float)f7;
+            f1.w = (float)f7;
+            float *f = feat + 8 * r;
+            f[0] = f0.x;
+            f[1] = f0.y;
+            f[2] = f0.z;
+            f[3] = f0.w;
+            f[4] = f1.x;
+            f[5] = f1.y;
+            f[6] = f1.z;
+            f[7] = f1.w;
         }
     }
 }
@@ -320,13 +357,19 @@ __global__ void __launch_bounds__(256) k_chain_cost(int64_t n, const float *__re
 
 }  // namespace
 
-hipError_t launch_features(const mcmi_cdf *cdf, double delta, int lmax, float *feat, hipStream_t s) {
-    const hipError_t fe = ensure_full_records(cdf, s);
-    if (fe != hipSuccess) return fe;
-    int64_t blocks = (cdf->n + 3) / 4;
+template <int P>
+hipError_t launch_features_p(const mcmi_cdf *cdf, double delta, int lmax, float *feat, hipStream_t s) {
+    int64_t blocks = (cdf->n * P + 255) / 256;
     if (blocks > 16384) blocks = 16384;
-    k_features<<<(unsigned)blocks, 256, 0, s>>>(cdf->n, cdf->rec, cdf->roff, delta, lmax, feat);
+    k_features<P><<<(unsigned)blocks, 256, 0, s>>>(cdf->n, cdf->rec32, cdf->roff, delta, lmax, feat);
     return hipGetLastError();
+}
+
+hipError_t launch_features(const mcmi_cdf *cdf, double delta, int lmax, float *feat, hipStream_t s) {
+    const double per_row = cdf->n > 0 ? (double)cdf->nnz_c / (double)cdf->n : 0.0;
+    if (per_row <= 10.0) return launch_features_p<4>(cdf, delta, lmax, feat, s);
+    if (per_row <= 40.0) return launch_features_p<16>(cdf, delta, lmax, feat, s);
+    return launch_features_p<64>(cdf, delta, lmax, feat, s);
 }
 
 size_t pilot_lds_bytes(int hash_slots, int cap) { return (size_t)hash_slots * 12u + 16u + (size_t)cap * 64u * 12u; }
@@ -474,7 +517,8 @@ extern "C" mcmi_status mcmi_chain_cost(const float *feat_dev, int64_t n, int32_t
     unsigned long long *tot = nullptr;
     MCMI_HIP(hipMallocAsync((void **)&tot, sizeof(unsigned long long), s));
     hipError_t e = hipMemsetAsync(tot, 0, sizeof(unsigned long long), s);
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
+    // one atomic per workgroup on one address: 512 workgroups (1M rows: 4096 took 53 us)
+    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 512);
     if (e == hipSuccess) {
         k_chain_cost<<<(unsigned)blocks, 256, 0, s>>>(n, feat_dev, cost_dev, tot);
         e = hipGetLastError();
