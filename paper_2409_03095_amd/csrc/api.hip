@@ -452,6 +452,12 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
             if (blocks * waves > pass_tasks) blocks = std::max<int64_t>(1, (pass_tasks + waves - 1) / waves);
             regions = blocks * waves;
         }
+        if (pass == 0 && !block_kernel && !p->pool_per_row && p->topk > 0 && pool_cap < ((int64_t)1 << 30)) {
+            // a pool of exactly topk entries per row has no room for what chunked
+            // reservations leave unused (ends of chunks, each wavefront's last chunk): the
+            // rows that then did not fit were walked again
+            pool_cap += pool_cap / 8 + regions * (int64_t)pool_chunk_for(pool_cap, regions);
+        }
         MCMI_HIP(pool_col[pass].alloc((size_t)pool_cap * sizeof(int32_t), s));
         MCMI_HIP(pool_val[pass].alloc((size_t)pool_cap * sizeof(double), s));
         pools.col[pass] = pool_col[pass].as<int32_t>();
