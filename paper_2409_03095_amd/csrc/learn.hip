@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(64) k_pilot(WalkArgs a, int pilot, int cap, do
     int *spill_cnt = (int *)(smem + (size_t)H * 12u);
     double *lv = (double *)(smem + (size_t)H * 12u + 16u);  // [slot][lane]
     i32x4v *lk = (i32x4v *)(smem + (size_t)H * 12u + 16u + (size_t)cap * 64u * 8u);  // [bucket][lane]
-    const uint32_t hmask = (uint32_t)H - 1u, smask = (uint32_t)a.spill_slots - 1u;
+    const uint32_t smask = (uint32_t)a.spill_slots - 1u;
     const i32x4v none = {kEmpty, kEmpty, kEmpty, kEmpty};
     for (int s = lane; s < H; s += 64) {
         keys[s] = kEmpty;
@@ -229,12 +229,12 @@ __global__ void __launch_bounds__(64) k_pilot(WalkArgs a, int pilot, int cap, do
                     bucket_issue<false>(a.rec, off, Hd, u, bl);
             }
             // contribution (j = 0 included: the start state gets W_0 = 1)
-            const uint32_t rb = hash_key(key, a.hash_shift) & ~3u;
+            const uint32_t rb = Probe<true, true, false>::home(key, (uint32_t)H, a.hash_shift);
             uint32_t pb = __umulhi((uint32_t)key * 0x9E3779B1u, nbk);
             int32_t rk[4];
             read_bucket_wave(keys, rb, rk);
             i32x4v pv = lk[pb * 64u + lane];
-            if (!lds_add_pre(keys, vals, hmask, rb, rk, key, w))
+            if (!Probe<true, true, false>::add(keys, vals, (uint32_t)H, rb, rk, key, w))
                 if (!spill_add(skeys, svals, sused, spill_cnt, smask, key, w)) spill_full = true;
             uint32_t tries = 0;
 #pragma unroll 1

@@ -133,10 +133,10 @@ struct ChainSt {
 // its key's home bucket read at the end of the previous step) and the Philox
 // block of the next four steps run while they are in flight. `blk` holds the
 // words of the chain's next draws (step j + 1 takes word j mod 4 of block j / 4).
-template <bool kF32, bool kCmp>
+template <bool kF32, bool kCmp, typename Tab>
 __device__ __forceinline__ void chain_step(const WalkArgs &a, ChainSt &ch, int stride, int32_t N, uint32_t r_off,
                                            const StepHdr &H0, uint32_t prow, uint32_t ptag, uint32_t k0, uint32_t k1,
-                                           int32_t *gkeys, double *gvals, uint32_t hmask, int hshift, int32_t *gskeys,
+                                           int32_t *gkeys, double *gvals, uint32_t slots, int hshift, int32_t *gskeys,
                                            double *gsvals, int32_t *gsused, int *gspill, uint32_t smask,
                                            unsigned long long &trans, unsigned long long &spilled, bool &spill_full) {
     const uint4 h = ch.H.h0;  // row, m, W, Shat32
@@ -167,7 +167,7 @@ __device__ __forceinline__ void chain_step(const WalkArgs &a, ChainSt &ch, int s
     }
     if (ch.j > 0) {
         const int32_t key = (int32_t)h.x;  // the row, or its compact record offset
-        if (!lds_add_pre(gkeys, gvals, hmask, ch.pb, ch.pk, key, wcur)) {
+        if (!Tab::add(gkeys, gvals, slots, ch.pb, ch.pk, key, wcur)) {
             ++spilled;
             if (!spill_add_window(gskeys, gsvals, gsused, gspill, smask, key, wcur)) spill_full = true;
         }
@@ -198,7 +198,7 @@ __device__ __forceinline__ void chain_step(const WalkArgs &a, ChainSt &ch, int s
         ++ch.j;
         // the next step adds this state's weight: its key's home bucket is read
         // now, so that the read has a whole bucket load's latency to complete
-        ch.pb = hash_key((int32_t)Nx.h0.x, hshift) & ~3u;
+        ch.pb = Tab::home((int32_t)Nx.h0.x, slots, hshift);
         read_bucket_wave(gkeys, ch.pb, ch.pk);
     }
 }
@@ -334,19 +334,20 @@ __device__ __forceinline__ bool finish_sorted(const WalkArgs &a, int32_t *tk, do
 // lane's own group's row); each lane keeps kC of its row's chains in flight.
 // kTop: with top-k retention (an instance of its own: its registers would not fit beside
 // the walk's in the common one).
-template <bool kF32, int kG, int kC, bool kCmp, bool kTop>
+template <bool kF32, int kG, int kC, bool kCmp, bool kTop, bool kWide>
 __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, RowPre &nxt, int &queue, int64_t &tlo,
                          int64_t &thi, int32_t *keys, double *vals, int *spill_cnt,
                          int32_t *skeys, double *svals, int32_t *sused, uint32_t k0, uint32_t k1,
                          unsigned long long &pcur, unsigned long long &pend, unsigned long long *wstats) {
     constexpr int P = 64 / kG;  // rows per wave
-    constexpr int kLogP = P == 1 ? 0 : P == 2 ? 1 : P == 4 ? 2 : 3;
     const int lane = lane_id();
     const int grp = lane / kG;
     const int sub = lane & (kG - 1);
     const int Hg = a.hash_slots / P;  // slots per row
+    const uint32_t slots = (uint32_t)Hg;
+    constexpr int kLogP = P == 1 ? 0 : P == 2 ? 1 : P == 4 ? 2 : 3;
     const int hshift = a.hash_shift + kLogP;
-    const uint32_t hmask = (uint32_t)Hg - 1u;
+    using Tab = Probe<!kWide, kC == 2 || !kF32, kWide>;
     const int Sg = a.spill_slots / P;
     const uint32_t smask = (uint32_t)Sg - 1u;
     int32_t *gkeys = keys + grp * Hg;
@@ -365,7 +366,12 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
     // Keys are rows, or record offsets with compact records (turned into rows once
     // the kept set is known).
     const int32_t rkey = kCmp ? (int32_t)r_off : r;
-    if (sub == 0 && has) lds_add<true>(gkeys, gvals, hmask, hash_key(rkey, hshift), rkey, (double)N);
+    if (sub == 0 && has) {
+        const uint32_t b = Tab::home(rkey, slots, hshift);
+        int32_t k[4];
+        read_bucket_wave(gkeys, b, k);
+        Tab::add(gkeys, gvals, slots, b, k, rkey, (double)N);
+    }
     wave_sync();
 
     // the row's own header (every chain starts there, loaded ahead); later
@@ -390,7 +396,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         // one chain per lane: a lane leaves the loop with its last chain (1024^2 grid with
         // per-row chains 7.9 -> 7.5 ms, 33 x 31 grid 150 -> 140 us against a wave vote per step)
         while (ch[0].active)
-            chain_step<kF32, kCmp>(a, ch[0], kG, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, hmask, hshift, gskeys,
+            chain_step<kF32, kCmp, Tab>(a, ch[0], kG, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, slots, hshift, gskeys,
                                    gsvals, gsused, spill_cnt + grp, smask, trans, spilled, spill_full);
     } else {
         while (true) {
@@ -401,7 +407,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
     #pragma unroll
             for (int k = 0; k < kC; ++k)
                 if (ch[k].active)
-                    chain_step<kF32, kCmp>(a, ch[k], kG * kC, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, hmask, hshift,
+                    chain_step<kF32, kCmp, Tab>(a, ch[k], kG * kC, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, slots, hshift,
                                      gskeys, gsvals, gsused, spill_cnt + grp, smask, trans, spilled, spill_full);
         }
     }
@@ -628,7 +634,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         // pair. When the value slots past the survivors have room, the sort moves
         // one word per entry, (column << 13) | position, in that free part of the
         // value table, and the values stay where they are; otherwise it moves
-        // (column, value) pairs, padding with INT32_MAX.
+        // (column, value) pairs.
         int PS = 1;
         while (PS < K) PS <<= 1;
         const bool packed = K + PS <= Hg;
@@ -672,16 +678,18 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
                 }
             }
         } else {
-            for (int s = K + lane; s < PS; s += 64) tk[s] = INT32_MAX;
-            wave_sync();
+            // (column, value) pairs in place. Every exchange leaves the smaller column in the
+            // lower slot (a merge of width k starts with the pairs i and k - 1 - i of its
+            // run), so the words past the survivors need no slots: they would stay
+            // where they are.
             for (int k = 2; k <= PS; k <<= 1) {
                 for (int jj = k >> 1; jj > 0; jj >>= 1) {
                     for (int pr = lane; pr < (PS >> 1); pr += 64) {
                         const int i = ((pr & ~(jj - 1)) << 1) | (pr & (jj - 1));
-                        const int ixj = i | jj;
+                        const int ixj = jj == k >> 1 ? i ^ (k - 1) : i | jj;
+                        if (ixj >= K) continue;
                         const int32_t ka = tk[i], kb = tk[ixj];
-                        const bool up = (i & k) == 0;
-                        if ((ka > kb) == up) {
+                        if (ka > kb) {
                             const double va = tv[i], vb = tv[ixj];
                             tk[i] = kb;
                             tk[ixj] = ka;
@@ -756,8 +764,10 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
     if (!hdr_issued) row_hdr<kF32, kCmp>(a, nxt);
 }
 
-template <bool kF32, int kG, int kC, bool kCmp, bool kTop>
-__global__ void __launch_bounds__(256, 3) k_walk(WalkArgs a) {
+// kWide: at most 128 registers, for four waves per SIMD where the tables of a launch leave
+// room for more than three (choose_shape).
+template <bool kF32, int kG, int kC, bool kCmp, bool kTop, bool kWide>
+__global__ void __launch_bounds__(256, kWide ? 4 : 3) k_walk(WalkArgs a) {
     constexpr int P = 64 / kG;
     extern __shared__ __align__(16) unsigned char smem[];
     const int waves = blockDim.x >> 6;
@@ -795,7 +805,7 @@ __global__ void __launch_bounds__(256, 3) k_walk(WalkArgs a) {
     row_hdr<kF32, kCmp>(a, cur);
     while (__any(cur.task >= 0)) {
         RowPre nxt;
-        walk_rows<kF32, kG, kC, kCmp, kTop>(a, cur, nxt, queue, tlo, thi, keys, vals, spill_cnt, skeys, svals, sused, k0,
+        walk_rows<kF32, kG, kC, kCmp, kTop, kWide>(a, cur, nxt, queue, tlo, thi, keys, vals, spill_cnt, skeys, svals, sused, k0,
                                       k1, pcur, pend, wstats);
         cur = nxt;
     }
@@ -813,18 +823,23 @@ __global__ void __launch_bounds__(256, 3) k_walk(WalkArgs a) {
 
 size_t walk_lds_bytes(int hash_slots, int waves) { return (size_t)waves * ((size_t)hash_slots * 12u + 64u); }
 
+// Whether a launch uses the four-waves-per-SIMD instance (one row per wave, one chain per lane).
+bool walk_wide(bool f32, bool top, int hash_slots) { return f32 && !top && hash_slots <= kWideSlots; }
+
 template <bool kF32, bool kCmp, bool kTop>
 hipError_t launch_walk_t(const WalkArgs &a, int blocks, int waves, hipStream_t s) {
     const size_t lds = walk_lds_bytes(a.hash_slots, waves);
     switch (a.row_lanes) {
-        case 8: k_walk<kF32, 8, 1, kCmp, kTop><<<blocks, waves * 64, lds, s>>>(a); break;
-        case 16: k_walk<kF32, 16, 1, kCmp, kTop><<<blocks, waves * 64, lds, s>>>(a); break;
-        case 32: k_walk<kF32, 32, 1, kCmp, kTop><<<blocks, waves * 64, lds, s>>>(a); break;
+        case 8: k_walk<kF32, 8, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a); break;
+        case 16: k_walk<kF32, 16, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a); break;
+        case 32: k_walk<kF32, 32, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a); break;
         default:
             if (a.lane_chains == 2)
-                k_walk<kF32, 64, 2, kCmp, kTop><<<blocks, waves * 64, lds, s>>>(a);
+                k_walk<kF32, 64, 2, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a);
+            else if (kF32 && !kTop && walk_wide(true, false, a.hash_slots))
+                k_walk<kF32, 64, 1, kCmp, kTop, kF32 && !kTop><<<blocks, waves * 64, lds, s>>>(a);
             else
-                k_walk<kF32, 64, 1, kCmp, kTop><<<blocks, waves * 64, lds, s>>>(a);
+                k_walk<kF32, 64, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a);
             break;
     }
     return hipGetLastError();
@@ -844,11 +859,16 @@ hipError_t launch_walk(const WalkArgs &a, bool f32, int blocks, int waves, hipSt
 }
 
 hipError_t walk_occupancy(bool f32, int hash_slots, int waves, int *blocks_per_cu) {
-    // the instances differ only in loop bounds; the 64-lane one stands for all
+    // the other instances differ only in loop bounds; the 64-lane one stands for all
     const size_t lds = walk_lds_bytes(hash_slots, waves);
+    if (walk_wide(f32, false, hash_slots))
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<true, 64, 1, true, false, true>,
+                                                            waves * 64, lds);
     if (f32)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<true, 64, 1, true, false>, waves * 64, lds);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<false, 64, 1, false, false>, waves * 64, lds);
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<true, 64, 1, true, false, false>,
+                                                            waves * 64, lds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<false, 64, 1, false, false, false>,
+                                                        waves * 64, lds);
 }
 
 }  // namespace mcmi

@@ -4,6 +4,10 @@
 
 namespace mcmi {
 
+// Largest LDS table (slots per wavefront) of which a CU holds sixteen: 160 KB / 16 =
+// 848 slots of 12 bytes and 64 bytes of counters.
+constexpr int kWideSlots = 848;
+
 struct WalkArgs {
     const uint32_t *rec;
     const uint32_t *rec32;         // compact records (FP32 walks)

@@ -13,6 +13,12 @@ __device__ __forceinline__ uint32_t hash_key(int32_t key, int shift) {
     return ((uint32_t)key * 2654435761u) >> shift;
 }
 
+// First slot of a key's home bucket in a table of nb buckets of four (any nb; the same
+// slots as hash_key's for a power of two).
+__device__ __forceinline__ uint32_t home_slot(int32_t key, uint32_t nb) {
+    return 4u * __umulhi((uint32_t)key * 2654435761u, nb);
+}
+
 // The LDS hash is probed a bucket of 4 slots at a time (two relaxed 64-bit
 // reads, or one 16-byte read where one wavefront owns the table), so a lookup in a table at moderate load ends after about one read
 // instead of walking a run of slots one by one; in a wavefront the slowest lane's
@@ -65,50 +71,78 @@ __device__ __forceinline__ int pick_slot(const int32_t k[4], int32_t key) {
     return s;
 }
 
-// lds_add for a table one wavefront owns, whose bucket b (the key's home bucket)
-// was read into k earlier, while the previous step's bucket load was in flight.
-// Hits and insertions take the same path (a compare-and-swap, which leaves a slot
-// that holds the key as it is): some lane of a wave inserts in most steps, so that
-// separate paths would both run (160^3 27-point walk 57.1 -> 55.3 ms, 128-chain
-// batched walk 24.9 -> 23.3 ms, 77^3 binary64 walk 9.8 -> 9.0 ms; a branch around
-// the compare-and-swap of hits: 59 ms). A copy that has gone stale is safe: keys never
-// move, slots fill lowest first, so the copy's slot for the key either is right or
-// has been taken by another key, which the compare-and-swap reports.
-__device__ __forceinline__ bool lds_add_pre(int32_t *keys, double *vals, uint32_t mask, uint32_t b, int32_t k[4],
-                                            int32_t key, double w) {
-    int nb = 0;
-#pragma unroll 1
-    for (;;) {
-        const int s = pick_slot(k, key);
-        if (s < 4) {
-            const int32_t prev = atomicCAS(&keys[b + s], kEmpty, key);
-            if ((prev ^ key) <= 0) {
-                atomicAdd(&vals[b + s], w);
-                return true;
-            }
-            // another key took the slot: read the bucket again
-        } else {
-            b = (b + 4u) & mask;
-            if (++nb >= kMaxLdsProbe / 4) return false;
-        }
-        read_bucket_wave(keys, b, k);
+// How a wavefront's table is probed.
+//  kPow2: a power of two of slots (else any multiple of four);
+//  kScatter: a key whose home bucket is full goes on 1 to 8 buckets further at a time by
+//    its hash, instead of to the next: fewer long runs of full buckets where tables fill
+//    up (128-chain batched walk 21.5 -> 21.2 ms, 77^3 binary64 7.95 -> 7.83; the 160^3
+//    FP32 walk 51.3 -> 51.5, so not there);
+//  kPeel: the first probe outside the loop (1024^2 grid with small tables 6.45 -> 6.25 ms; the
+//    160^3 walk 51.2 -> 53.6 and the batched one 20.1 -> 21.0, so not there).
+template <bool kPow2, bool kScatter, bool kPeel>
+struct Probe {
+    static __device__ __forceinline__ uint32_t home(int32_t key, uint32_t slots, int shift) {
+        return kPow2 ? hash_key(key, shift) & ~3u : home_slot(key, slots / 4u);
     }
-}
+    static __device__ __forceinline__ uint32_t next(uint32_t b, int32_t key, uint32_t slots) {
+        b += kScatter ? 4u + (((uint32_t)key * 2654435761u) & 28u) : 4u;
+        if (kPow2) return b & (slots - 1u);
+        return b >= slots ? b - slots : b;
+    }
+    // Adds w to key's slot of a table one wavefront owns, inserting the key if absent; b is
+    // the key's home bucket, read into k earlier, while the previous step's bucket load was
+    // in flight. False when kMaxLdsProbe slots of its sequence are held by other keys.
+    // Hits and insertions take the same path (a compare-and-swap, which leaves a slot
+    // that holds the key as it is): some lane of a wave inserts in most steps, so that
+    // separate paths would both run (160^3 27-point walk 57.1 -> 55.3 ms, 128-chain
+    // batched walk 24.9 -> 23.3 ms, 77^3 binary64 walk 9.8 -> 9.0 ms; a branch around
+    // the compare-and-swap of hits: 59 ms). A copy that has gone stale is safe: keys never
+    // move, slots fill lowest first, so the copy's slot for the key either is right or
+    // has been taken by another key, which the compare-and-swap reports.
+    static __device__ __forceinline__ bool add(int32_t *keys, double *vals, uint32_t slots, uint32_t b, int32_t k[4],
+                                               int32_t key, double w) {
+        int s = pick_slot(k, key);
+        if (kPeel) {
+            bool done = false;
+            if (s < 4) {
+                const int32_t prev = atomicCAS(&keys[b + s], kEmpty, key);
+                done = (prev ^ key) <= 0;
+                if (done) atomicAdd(&vals[b + s], w);
+            }
+            if (done) return true;
+            if (s == 4) b = next(b, key, slots);
+            read_bucket_wave(keys, b, k);
+            s = pick_slot(k, key);
+        }
+        int nb = kPeel ? 1 : 0;
+#pragma unroll 1
+        for (;;) {
+            if (s < 4) {
+                const int32_t prev = atomicCAS(&keys[b + s], kEmpty, key);
+                if ((prev ^ key) <= 0) {
+                    atomicAdd(&vals[b + s], w);
+                    return true;
+                }
+                // another key took the slot: read the bucket again
+            } else {
+                b = next(b, key, slots);
+                if (++nb >= kMaxLdsProbe / 4) return false;
+            }
+            read_bucket_wave(keys, b, k);
+            s = pick_slot(k, key);
+        }
+    }
+};
 
 // Adds w to key's slot, inserting the key if absent; false when the kMaxLdsProbe
 // slots from the key's bucket on are all held by other keys.
-// kWave: the table belongs to one wavefront (16-byte bucket reads)
-template <bool kWave = false>
 __device__ __forceinline__ bool lds_add(int32_t *keys, double *vals, uint32_t mask, uint32_t h, int32_t key,
                                         double w) {
     uint32_t b = h & ~3u;
     int nb = 0;
     while (nb < kMaxLdsProbe / 4) {
         int32_t k[4];
-        if (kWave)
-            read_bucket_wave(keys, b, k);
-        else
-            read_bucket(keys, b, k);
+        read_bucket(keys, b, k);
         int hit, emp;
         scan_bucket(k, key, hit, emp);
         if (hit >= 0) {
