@@ -400,8 +400,9 @@ typedef struct {
  * when ||r|| <= rtol ||b|| for the recurrence residual r, or after maxiter
  * iterations, or on a breakdown (a zero inner product); then converged = 0 and x
  * holds the last iterate. Dot products reduce in a fixed order, so a rerun gives
- * the same iterates. Allocates 8 n float64 of workspace; synchronises the stream
- * once per inner product. */
+ * the same iterates. Allocates 8 n float64 and 56 KiB of workspace; the host
+ * queues iterations ahead of the one whose status it reads, and the stream is
+ * drained when the call returns. */
 mcmi_status mcmi_bicgstab(const mcmi_csr_in *B, const mcmi_csr_out *M, const double *b_dev, double *x_dev,
                           double rtol, int32_t maxiter, mcmi_solve_stats *st, void *stream);
 

@@ -4,14 +4,16 @@
 // last paragraph; the solver experiments of Section VI). This is van der Vorst's
 // BiCGstab with M applied on the right (solve B M y = b, x = M y): every step
 // applies B and M once per half step (CSR SpMV), and each vector update also forms
-// the partial sums of the inner products that follow it, which the last workgroup to
-// arrive adds in index order (a fixed order: reruns give the same iterates). That
-// workgroup then forms the step's scalars on the device, so an iteration is 7 launches (9
-// with M) with no host round trip in it; every kernel returns at once when the
-// solve has ended. The host queues up to kAhead iterations ahead and reads the status word
-// that the last launch of an iteration leaves in host memory. On a 100 x 77 5-point
-// grid (45 iterations) an inner product's two launches, copy and wait, six times
-// per iteration, took 7.6 of 7.7 ms.
+// the workgroups' partial sums of the inner products that follow it. The kernel that needs
+// such a product adds the partials itself, in every workgroup (in a fixed order: reruns
+// give the same iterates) and forms the step's scalars from it, so an iteration is 7
+// launches (9 with M) with no host round trip, and no workgroup waits for another;
+// workgroup 0 keeps the scalars that later kernels read. Every kernel returns at once when
+// the solve has ended. The host queues up to kAhead iterations ahead and reads the
+// status word that a launch leaves in host memory. A 100 x 77 5-point grid (45 iterations)
+// took 7.4 ms with two launches, a copy and a wait per inner product, 1.44 ms with the
+// partials added by the last workgroup to arrive, and takes 1.28 ms so; a 64^3 27-point
+// stencil with its M (1024 partials to a product) took 2.9 / 1.73 / 1.06 ms.
 #include <math.h>
 #include <string.h>
 
@@ -30,213 +32,217 @@ namespace {
 constexpr int kDotBlocks = 1024;  // most workgroups of an inner product
 constexpr int kAhead = 3;         // iterations queued past the one whose status is read
 
+// kHalf: converged in the half step of iteration half_it, whose last launch updates x
 enum Status : int32_t { kRun = 0, kConverged = 1, kHalf = 2, kBreakdown = 3, kZeroRhs = 4 };
 
-// Scalars of a solve (device memory).
+// Scalars of a solve (device memory), written by workgroup 0. A kernel reads none that it
+// writes, but for the status, whose late readers only return early where all do: rho of
+// an iteration is kept under its parity.
 struct KState {
-    int32_t status;  // kHalf: converged in the half step, x not yet updated
-    uint32_t arrived;
-    int64_t it, maxiter;
-    double rtol, bnrm, rr, ss, rho, alpha, beta, omega;
+    int32_t status, pad;
+    int64_t it, half_it;
+    double bnrm, rr, alpha, omega, rho[2];
 };
 
-// The workgroup's sums of acc[0 .. K) into part[k kDotBlocks + block]; true in the last
-// workgroup of the grid, with the totals in tot (all threads), each added over
-// the blocks in a fixed order.
-template <int K>
-__device__ __forceinline__ bool finish_sums(const double (&acc)[K], double *part, KState *st, double (&tot)[K]) {
-    __shared__ double red[K][4];
-    __shared__ int last;
-    const int t = threadIdx.x, w = t >> 6;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double a = wave_sum(acc[k]);
-        if ((t & 63) == 0) red[k][w] = a;
-    }
+// Partial sums, kDotBlocks per inner product.
+enum Part { kBB = 0, kRR = 1, kRhatR = 2, kRhatV = 3, kSS = 4, kTS = 5, kTT = 6, kParts = 7 };
+
+struct Scalars {
+    KState *st;
+    double *part;
+    int32_t *host_status;  // in host memory
+    double rtol;
+};
+
+// the workgroup's sum of acc into its place of product `which`
+__device__ __forceinline__ void put_partial(const Scalars &c, int which, double acc) {
+    __shared__ double red[4];
+    acc = wave_sum(acc);
     __syncthreads();
-    if (t == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            __hip_atomic_store(part + k * kDotBlocks + blockIdx.x,
-                               (red[k][0] + red[k][1]) + (red[k][2] + red[k][3]), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        last = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
-               gridDim.x - 1u;
-    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (!last) return false;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double a = 0.0;
-        for (int i = t; i < (int)gridDim.x; i += 256)
-            a += __hip_atomic_load(part + k * kDotBlocks + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        a = wave_sum(a);
-        if ((t & 63) == 0) red[k][w] = a;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) tot[k] = (red[k][0] + red[k][1]) + (red[k][2] + red[k][3]);
-    if (t == 0) st->arrived = 0u;
-    return true;
+    if (threadIdx.x == 0) c.part[which * kDotBlocks + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// ||b||, and the solve's constants
-__global__ void __launch_bounds__(256) k_norm_b(int64_t n, const double *__restrict__ b, double rtol, int64_t maxiter,
-                                                double *part, KState *st) {
-    double acc[1] = {0.0}, tot[1];
+// the whole product, in every thread (all the solve's kernels have the same grid)
+__device__ __forceinline__ double total(const Scalars &c, int which) {
+    __shared__ double red[4];
+    double a = 0.0;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += 256) a += c.part[which * kDotBlocks + i];
+    a = wave_sum(a);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+__device__ __forceinline__ bool first_thread() { return blockIdx.x == 0 && threadIdx.x == 0; }
+
+// (workgroup 0) the solve ends with `status` after `it` iterations
+__device__ __forceinline__ void end_solve(const Scalars &c, int32_t status, int64_t it) {
+    c.st->it = it;
+    c.st->status = status;
+    __hip_atomic_store(c.host_status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// b . b
+__global__ void __launch_bounds__(256) k_norm_b(int64_t n, const double *__restrict__ b, Scalars c) {
+    double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) acc[0] += b[i] * b[i];
-    if (!finish_sums<1>(acc, part, st, tot) || threadIdx.x != 0) return;
-    st->bnrm = sqrt(tot[0]);
-    st->rtol = rtol;
-    st->maxiter = maxiter;
-    st->it = 0;
-    st->alpha = st->omega = 1.0;
-    st->beta = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) acc += b[i] * b[i];
+    put_partial(c, kBB, acc);
 }
 
-// r = b - y, rhat = r; ||r||^2
+// r = b - y, rhat = r; ||r||^2 (and rhat . r)
 __global__ void __launch_bounds__(256) k_residual(int64_t n, const double *__restrict__ b,
                                                   const double *__restrict__ y, double *__restrict__ r,
-                                                  double *__restrict__ rhat, double *part, KState *st) {
-    double acc[1] = {0.0}, tot[1];
+                                                  double *__restrict__ rhat, Scalars c) {
+    double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const double v = b[i] - y[i];
         r[i] = v;
         rhat[i] = v;
-        acc[0] += v * v;
+        acc += v * v;
     }
-    if (!finish_sums<1>(acc, part, st, tot) || threadIdx.x != 0) return;
-    st->rr = tot[0];
-    st->rho = tot[0];  // rhat . r
-    if (st->bnrm == 0.0)
-        st->status = kZeroRhs;
-    else if (sqrt(tot[0]) <= st->rtol * st->bnrm)
-        st->status = kConverged;
+    put_partial(c, kRR, acc);
+    put_partial(c, kRhatR, acc);
 }
 
-// p = r + beta (p - omega v) (p = r in the first iteration); x = 0 when b = 0
-__global__ void __launch_bounds__(256) k_dir(int64_t n, const double *__restrict__ r, const double *__restrict__ v,
-                                             double *__restrict__ p, double *__restrict__ x,
-                                             const KState *__restrict__ st) {
-    const int32_t status = st->status;
+// Iteration `it` begins: the state of the residual, then p = r + beta (p - omega v)
+// (p = r in the first iteration); x = 0 when b = 0.
+__global__ void __launch_bounds__(256) k_dir(int64_t n, int64_t it, const double *__restrict__ r,
+                                             const double *__restrict__ v, double *__restrict__ p,
+                                             double *__restrict__ x, Scalars c) {
+    const int32_t status = c.st->status;
+    if (status != kRun && status != kZeroRhs) return;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (status == kZeroRhs)
+    const double bnrm = it == 1 ? sqrt(total(c, kBB)) : c.st->bnrm;
+    if (bnrm == 0.0) {
         for (int64_t i = i0; i < n; i += stride) x[i] = 0.0;
-    if (status != kRun) return;
-    if (st->it == 0) {
-        for (int64_t i = i0; i < n; i += stride) p[i] = r[i] + 0.0;
+        if (first_thread()) end_solve(c, kZeroRhs, 0);
         return;
     }
-    const double beta = st->beta, omega = st->omega;
-    for (int64_t i = i0; i < n; i += stride) p[i] = r[i] + beta * (p[i] - omega * v[i]);
+    const double rr = total(c, kRR), rho = total(c, kRhatR);
+    const double omega = it == 1 ? 1.0 : c.st->omega;
+    if (first_thread()) {
+        c.st->bnrm = bnrm;
+        c.st->rr = rr;
+        c.st->rho[it & 1] = rho;
+    }
+    if (sqrt(rr) <= c.rtol * bnrm || omega == 0.0) {
+        if (first_thread()) end_solve(c, sqrt(rr) <= c.rtol * bnrm ? kConverged : kBreakdown, it - 1);
+        return;
+    }
+    if (rho == 0.0) {
+        if (first_thread()) end_solve(c, kBreakdown, it);
+        return;
+    }
+    if (it == 1) {
+        for (int64_t i = i0; i < n; i += stride) p[i] = r[i] + 0.0;
+    } else {
+        const double beta = (rho / c.st->rho[(it - 1) & 1]) * (c.st->alpha / omega);
+        for (int64_t i = i0; i < n; i += stride) p[i] = r[i] + beta * (p[i] - omega * v[i]);
+    }
+    if (first_thread()) c.st->it = it;
 }
 
-// alpha = rho / (rhat . v)
-__global__ void __launch_bounds__(256) k_alpha(int64_t n, const double *__restrict__ rhat,
-                                               const double *__restrict__ v, double *part, KState *st) {
-    if (st->status != kRun) return;
-    double acc[1] = {0.0}, tot[1];
+// rhat . v
+__global__ void __launch_bounds__(256) k_rhat_v(int64_t n, const double *__restrict__ rhat,
+                                                const double *__restrict__ v, Scalars c) {
+    if (c.st->status != kRun) return;
+    double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) acc[0] += rhat[i] * v[i];
-    if (!finish_sums<1>(acc, part, st, tot) || threadIdx.x != 0) return;
-    st->it += 1;
-    if (tot[0] == 0.0)
-        st->status = kBreakdown;
-    else
-        st->alpha = st->rho / tot[0];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) acc += rhat[i] * v[i];
+    put_partial(c, kRhatV, acc);
 }
 
-// s = r - alpha v; ||s||^2
-__global__ void __launch_bounds__(256) k_half(int64_t n, const double *__restrict__ r, const double *__restrict__ v,
-                                              double *__restrict__ sv, double *part, KState *st) {
-    if (st->status != kRun) return;
-    const double a = -st->alpha;
-    double acc[1] = {0.0}, tot[1];
+// alpha = rho / (rhat . v); s = r - alpha v; ||s||^2
+__global__ void __launch_bounds__(256) k_half(int64_t n, int64_t it, const double *__restrict__ r,
+                                              const double *__restrict__ v, double *__restrict__ sv, Scalars c) {
+    if (c.st->status != kRun) return;
+    const double rv = total(c, kRhatV);
+    if (rv == 0.0) {
+        if (first_thread()) end_solve(c, kBreakdown, it);
+        return;
+    }
+    const double alpha = c.st->rho[it & 1] / rv, a = -alpha;
+    double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const double s = r[i] + a * v[i];
         sv[i] = s;
-        acc[0] += s * s;
+        acc += s * s;
     }
-    if (!finish_sums<1>(acc, part, st, tot) || threadIdx.x != 0) return;
-    st->ss = tot[0];
-    if (sqrt(tot[0]) <= st->rtol * st->bnrm) st->status = kHalf;
+    put_partial(c, kSS, acc);
+    if (first_thread()) c.st->alpha = alpha;
 }
 
-// omega = (t . s) / (t . t)
-__global__ void __launch_bounds__(256) k_omega(int64_t n, const double *__restrict__ t, const double *__restrict__ sv,
-                                               double *part, KState *st) {
-    if (st->status != kRun) return;
-    double acc[2] = {0.0, 0.0}, tot[2];
+// t . s and t . t, unless the half step has converged
+__global__ void __launch_bounds__(256) k_t_dots(int64_t n, int64_t it, const double *__restrict__ t,
+                                                const double *__restrict__ sv, Scalars c) {
+    if (c.st->status != kRun) return;
+    const double ss = total(c, kSS);
+    if (sqrt(ss) <= c.rtol * c.st->bnrm) {
+        if (first_thread()) {
+            c.st->rr = ss;
+            c.st->half_it = it;
+            end_solve(c, kHalf, it);
+        }
+        return;
+    }
+    double ts = 0.0, tt = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const double ti = t[i];
-        acc[0] += ti * sv[i];
-        acc[1] += ti * ti;
+        ts += ti * sv[i];
+        tt += ti * ti;
     }
-    if (!finish_sums<2>(acc, part, st, tot) || threadIdx.x != 0) return;
-    if (tot[1] == 0.0)
-        st->status = kBreakdown;
-    else
-        st->omega = tot[0] / tot[1];
+    put_partial(c, kTS, ts);
+    put_partial(c, kTT, tt);
 }
 
-// x += alpha phat + omega shat, r = s - omega t; ||r||^2 and rhat . r. After a converged
-// half step only x += alpha phat. The last launch of an iteration: it leaves the
-// status in host memory.
-__global__ void __launch_bounds__(256) k_step(int64_t n, const double *__restrict__ phat,
+// omega = (t . s) / (t . t); x += alpha phat + omega shat, r = s - omega t; ||r||^2 and
+// rhat . r. After a converged half step only x += alpha phat.
+__global__ void __launch_bounds__(256) k_step(int64_t n, int64_t it, const double *__restrict__ phat,
                                               const double *__restrict__ shat, const double *__restrict__ sv,
                                               const double *__restrict__ t, const double *__restrict__ rhat,
-                                              double *__restrict__ x, double *__restrict__ r, double *part, KState *st,
-                                              int32_t *host_status) {
-    const int32_t status = st->status;
+                                              double *__restrict__ x, double *__restrict__ r, Scalars c) {
+    const int32_t status = c.st->status;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double acc[2] = {0.0, 0.0}, tot[2];
-    if (status == kHalf) {
-        const double alpha = st->alpha;
+    if (status == kHalf && c.st->half_it == it) {
+        const double alpha = c.st->alpha;
         for (int64_t i = i0; i < n; i += stride) x[i] = x[i] + alpha * phat[i];
-        if (!finish_sums<2>(acc, part, st, tot) || threadIdx.x != 0) return;
-        st->rr = st->ss;
-        st->status = kConverged;
-        __hip_atomic_store(host_status, (int32_t)kConverged, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (status != kRun) return;
+    const double ts = total(c, kTS), tt = total(c, kTT);
+    if (tt == 0.0) {
+        if (first_thread()) end_solve(c, kBreakdown, it);
         return;
     }
-    if (status != kRun) {
-        if (i0 == 0) __hip_atomic_store(host_status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        return;
-    }
-    const double alpha = st->alpha, omega = st->omega;
+    const double alpha = c.st->alpha, omega = ts / tt;
+    double rr = 0.0, rho = 0.0;
     for (int64_t i = i0; i < n; i += stride) {
         x[i] = x[i] + alpha * phat[i] + omega * shat[i];
         const double ri = sv[i] - omega * t[i];
         r[i] = ri;
-        acc[0] += ri * ri;
-        acc[1] += rhat[i] * ri;
+        rr += ri * ri;
+        rho += rhat[i] * ri;
     }
-    if (!finish_sums<2>(acc, part, st, tot) || threadIdx.x != 0) return;
-    st->rr = tot[0];
-    int32_t now = kRun;
-    if (sqrt(tot[0]) <= st->rtol * st->bnrm) {
-        now = kConverged;
-    } else if (omega == 0.0) {
-        now = kBreakdown;
-    } else {
-        const double rho_prev = st->rho, rho = tot[1];
-        st->rho = rho;
-        st->beta = (rho / rho_prev) * (alpha / omega);
-        if (rho == 0.0 && st->it < st->maxiter) {  // found at the start of the next iteration
-            st->it += 1;
-            now = kBreakdown;
-        }
-    }
-    if (now != kRun) {
-        st->status = now;
-        __hip_atomic_store(host_status, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    put_partial(c, kRR, rr);
+    put_partial(c, kRhatR, rho);
+    if (first_thread()) c.st->omega = omega;
+}
+
+// after the last iteration: its residual (same grid, one workgroup does the work)
+__global__ void __launch_bounds__(256) k_last(Scalars c) {
+    if (blockIdx.x != 0 || c.st->status != kRun) return;
+    const double rr = total(c, kRR);
+    if (threadIdx.x != 0) return;
+    c.st->rr = rr;
+    if (sqrt(rr) <= c.rtol * c.st->bnrm) c.st->status = kConverged;
 }
 
 unsigned grid_dot(int64_t n) {
@@ -310,14 +316,14 @@ extern "C" mcmi_status mcmi_bicgstab(const mcmi_csr_in *B, const mcmi_csr_out *M
         *(volatile int32_t *)status = kRun;
         void *sdev = nullptr;
         if (!ok(hipHostGetDevicePointer(&sdev, status, 0))) return false;
-        int32_t *status_dev = (int32_t *)sdev;
-        if (!ok(dev_alloc((void **)&w, 8 * vec + 2 * kDotBlocks * sizeof(double) + sizeof(KState), s))) return false;
+        if (!ok(dev_alloc((void **)&w, 8 * vec + kParts * kDotBlocks * sizeof(double) + sizeof(KState), s))) return false;
         double *r = w, *rhat = w + n, *p = w + 2 * n, *v = w + 3 * n, *sv = w + 5 * n, *t = w + 7 * n;
         // without M, phat = p and shat = s
         double *phat = M ? w + 4 * n : p, *shat = M ? w + 6 * n : sv;
         double *part = w + 8 * n;
-        KState *st_dev = (KState *)(part + 2 * kDotBlocks);
+        KState *st_dev = (KState *)(part + kParts * kDotBlocks);
         const int32_t *stop = &st_dev->status;
+        const Scalars c{st_dev, part, (int32_t *)sdev, rtol};
         const unsigned g = grid_dot(n);
         auto applyB = [&](const double *x, double *y) {
             return ok(spmv(n, B->nnz, B->row_ptr_dev, B->col_dev, B->val_dev, x, y, stop, s));
@@ -327,22 +333,24 @@ extern "C" mcmi_status mcmi_bicgstab(const mcmi_csr_in *B, const mcmi_csr_out *M
         };
         if (!ok(hipEventRecord(e0, s))) return false;
         if (!ok(hipMemsetAsync(st_dev, 0, sizeof(KState), s))) return false;
-        k_norm_b<<<g, 256, 0, s>>>(n, b_dev, rtol, maxiter, part, st_dev);
+        k_norm_b<<<g, 256, 0, s>>>(n, b_dev, c);
         if (!applyB(x_dev, v)) return false;
-        k_residual<<<g, 256, 0, s>>>(n, b_dev, v, r, rhat, part, st_dev);
+        k_residual<<<g, 256, 0, s>>>(n, b_dev, v, r, rhat, c);
         for (int64_t it = 1; it <= maxiter; ++it) {
-            k_dir<<<g, 256, 0, s>>>(n, r, v, p, x_dev, st_dev);
+            k_dir<<<g, 256, 0, s>>>(n, it, r, v, p, x_dev, c);
             if (!applyM(p, phat) || !applyB(phat, v)) return false;
-            k_alpha<<<g, 256, 0, s>>>(n, rhat, v, part, st_dev);
-            k_half<<<g, 256, 0, s>>>(n, r, v, sv, part, st_dev);
+            k_rhat_v<<<g, 256, 0, s>>>(n, rhat, v, c);
+            k_half<<<g, 256, 0, s>>>(n, it, r, v, sv, c);
             if (!applyM(sv, shat) || !applyB(shat, t)) return false;
-            k_omega<<<g, 256, 0, s>>>(n, t, sv, part, st_dev);
-            k_step<<<g, 256, 0, s>>>(n, phat, shat, sv, t, rhat, x_dev, r, part, st_dev, status_dev);
+            k_t_dots<<<g, 256, 0, s>>>(n, it, t, sv, c);
+            k_step<<<g, 256, 0, s>>>(n, it, phat, shat, sv, t, rhat, x_dev, r, c);
             if (!ok(hipGetLastError())) return false;
             if (!ok(hipEventRecord(ev[it % (kAhead + 1)], s))) return false;
             if (it > kAhead && !ok(hipEventSynchronize(ev[(it - kAhead) % (kAhead + 1)]))) return false;
             if (*(volatile int32_t *)status != kRun) break;
         }
+        k_last<<<g, 256, 0, s>>>(c);
+        if (!ok(hipGetLastError())) return false;
         if (!ok(hipEventRecord(e1, s))) return false;
         if (!ok(hipMemcpyAsync(&h, st_dev, sizeof(h), hipMemcpyDeviceToHost, s))) return false;
         return ok(hipStreamSynchronize(s));
@@ -362,7 +370,7 @@ extern "C" mcmi_status mcmi_bicgstab(const mcmi_csr_in *B, const mcmi_csr_out *M
         st->iterations = h.it;
         st->rel_residual = h.bnrm > 0.0 ? sqrt(h.rr) / h.bnrm : 0.0;
         st->ms = ms;
-        st->converged = h.status == kConverged || h.status == kZeroRhs;
+        st->converged = h.status == kConverged || h.status == kHalf || h.status == kZeroRhs;
     }
     return MCMI_OK;
 }
