@@ -95,16 +95,34 @@ __device__ __forceinline__ void block_max_bits(unsigned long long *bits, double 
     }
 }
 
-// ||B||_inf for the augmented splitting: each thread sums one row's |b_ij| in
+// ||B||_inf for the augmented splitting: each lane sums one row's |b_ij| in
 // column order (one IEEE add at a time, so the sums are those of a sequential
-// loop), the maximum is an integer max on the bits of the non-negative sums.
-__global__ void __launch_bounds__(256) k_row_abs_max(int64_t n, const int64_t *__restrict__ rp,
-                                                     const double *__restrict__ v, unsigned long long *bits) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+// loop), the maximum is an integer max on the bits of the non-negative sums. A
+// wavefront's 64 rows are one run of entries, which comes through LDS in pieces of
+// kAbsChunk so that the loads are consecutive (64^3 27-point matrix: 63 us with each
+// lane reading its row, 30 us so).
+constexpr int kAbsChunk = 1024;
+
+__global__ void __launch_bounds__(64) k_row_abs_max(int64_t n, int64_t nnz, const int64_t *__restrict__ rp,
+                                                    const double *__restrict__ v, unsigned long long *bits) {
+    __shared__ double chunk[kAbsChunk];
+    const int lane = threadIdx.x;
     double best = 0.0;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += stride) {
+    for (int64_t r0 = (int64_t)blockIdx.x * 64; r0 < n; r0 += (int64_t)gridDim.x * 64) {
+        const int64_t r = r0 + lane, last = r0 + 64 < n ? r0 + 64 : n;
+        const int64_t begin = rp[r0], end = rp[last];
+        if (begin < 0 || end > nnz) continue;  // (k_count refuses the matrix)
+        const int64_t b = r < n ? rp[r] : end, e = r < n ? rp[r + 1] : end;
+        int64_t k = b < begin ? e : b;
         double sum = 0.0;
-        for (int64_t k = rp[r]; k < rp[r + 1]; ++k) sum += fabs(v[k]);
+        for (int64_t c0 = begin; c0 < end; c0 += kAbsChunk) {
+            const int cn = end - c0 < kAbsChunk ? (int)(end - c0) : kAbsChunk;
+            __syncthreads();
+            for (int i = lane; i < cn; i += 64) chunk[i] = v[c0 + i];
+            __syncthreads();
+            const int64_t ke = e < c0 + cn ? e : c0 + cn;
+            for (; k >= c0 && k < ke; ++k) sum += fabs(chunk[k - c0]);
+        }
         best = sum > best ? sum : best;
     }
     block_max_bits(bits, best);
@@ -327,26 +345,18 @@ __global__ void __launch_bounds__(256) k_fill(int64_t n, const int64_t *__restri
 // q_l -= W - q_s), and l goes back on small if q_l < W, else on large. Leftover
 // buckets keep all W units (T = W, A = self). Every entry's final q is its
 // threshold. Both stacks live in one scratch array of the row's length (small
-// grows up from the front, large down from the back), q and A in two more, at
-// stride sc (vose_row); the scratch is in LDS for rows of up to kAliasLds
-// entries (in the row's slice of a global scratch otherwise). The thresholds and
-// alias indices end in thr_g and ali_g, indexed like the entries of C.
+// grows up from the front, large down from the back), q (filled by the caller) and A in
+// two more, at stride sc.
 constexpr int kAliasLds = 32;    // rows up to this long keep their scratch in LDS
-constexpr int kAliasPitch = 65;  // LDS words per entry index: the lanes of a wave hit distinct banks
+constexpr int kAliasRows = 16;   // most rows that a wave takes together
+constexpr int kAliasPitch = 17;  // LDS words per entry index: the rows hit distinct banks
 
 template <typename I>
-__device__ __forceinline__ void vose_row(uint32_t m, const uint2 *__restrict__ row, uint32_t *q, I *st, I *al,
-                                         int sc) {
-    const uint32_t W = row[m - 1].x;
+__device__ __forceinline__ void vose_row(uint32_t m, uint32_t W, uint32_t *q, I *st, I *al, int sc) {
     int ns = 0, nl = 0;
-    uint32_t prev = 0;
     for (uint32_t k = 0; k < m; ++k) {
-        const uint32_t cum = row[k].x;
-        const uint32_t qk = m * (cum - prev);  // m w_k <= m 2^Q <= 2^31
-        prev = cum;
-        q[k * sc] = qk;
         al[k * sc] = (I)k;
-        if (qk < W)
+        if (q[k * sc] < W)
             st[(ns++) * sc] = (I)k;
         else
             st[(m - 1 - nl++) * sc] = (I)k;
@@ -364,37 +374,8 @@ __device__ __forceinline__ void vose_row(uint32_t m, const uint2 *__restrict__ r
     }
 }
 
-// LDS rows keep their stack and alias indices in bytes (entry indices < 32):
-// 12.5 KB per wave instead of 25 KB, twice the waves per CU.
-__global__ void __launch_bounds__(64) k_alias(int64_t n, const uint32_t *__restrict__ mrow,
-                                              const int64_t *__restrict__ cptr, const uint2 *__restrict__ sorted,
-                                              uint32_t *__restrict__ thr_g, int32_t *__restrict__ stk_g,
-                                              int32_t *__restrict__ ali_g) {
-    __shared__ uint32_t q_l[kAliasLds * kAliasPitch];
-    __shared__ uint8_t st_l[kAliasLds * kAliasPitch];
-    __shared__ uint8_t al_l[kAliasLds * kAliasPitch];
-    const int lane = threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + lane; r < n; r += stride) {
-        const uint32_t m = mrow[r];
-        if (m == 0) continue;
-        const int64_t base = cptr[r];
-        if (m <= (uint32_t)kAliasLds) {
-            vose_row<uint8_t>(m, sorted + base, q_l + lane, st_l + lane, al_l + lane, kAliasPitch);
-            for (uint32_t k = 0; k < m; ++k) {
-                thr_g[base + k] = q_l[k * kAliasPitch + lane];
-                ali_g[base + k] = (int32_t)al_l[k * kAliasPitch + lane];
-            }
-        } else {
-            vose_row<int32_t>(m, sorted + base, thr_g + base, stk_g + base, ali_g + base, 1);
-        }
-    }
-}
-
 constexpr int kBucketSlots = 4;
-// buckets per lane in flight in k_buckets32: fewer registers, more waves (on the
-// 160^3 27-point records 1.83 ms with 2, 1.93 ms with 4, 2.60 ms with 8)
-constexpr int kBucketSlots32 = 2;
+constexpr int kBucketSlots32 = 2;  // buckets per lane in flight in k_buckets32
 
 // Full records from the compact ones (see common.hpp). Header units: thread per
 // row. Buckets: a wave takes 64 consecutive rows and writes their buckets as one
@@ -482,39 +463,76 @@ __global__ void __launch_bounds__(256) k_expand_buckets(int64_t n, const uint32_
     }
 }
 
-// The compact buckets (8 words each, see common.hpp): a wave takes 64
-// consecutive rows as in k_expand_buckets, two lanes per bucket (its own half, its alias
-// half) and 32 buckets per pass; the targets' record offsets, m and Shat32 come
-// from the dense per-row table k_fill writes (16 bytes a row, so that neighbouring
-// targets share cache lines, which their header units spread over the records
-// do not).
-__global__ void __launch_bounds__(256) k_buckets32(int64_t n, const uint32_t *__restrict__ mrow,
-                                                   const uint32_t *__restrict__ roff32,
-                                                   const int64_t *__restrict__ cptr, const uint2 *__restrict__ sorted,
-                                                   const uint32_t *__restrict__ thr_g,
-                                                   const int32_t *__restrict__ ali_g, const uint4 *__restrict__ tinfo,
-                                                   uint32_t *__restrict__ rec32, int rows_per_wave) {
-    __shared__ uint32_t pm_s[4][65];
-    __shared__ int64_t pb_s[4][64];
-    __shared__ uint32_t po_s[4][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t *pm = pm_s[wv];
-    int64_t *pb = pb_s[wv];
-    uint32_t *po = po_s[wv];
-    const int64_t wstride = (int64_t)gridDim.x * 4 * rows_per_wave;
-    for (int64_t r0 = ((int64_t)blockIdx.x * 4 + wv) * rows_per_wave; r0 < n; r0 += wstride) {
+// ceil(T 2^32 / W) for T < W <= 2^31, inv = 1 / W: the FP64 quotient's integer part is
+// within one of the exact one, and the remainder says which way (the 64-bit integer
+// division takes several times the instructions).
+__device__ __forceinline__ uint32_t ceil_frac32(uint32_t T, uint32_t W, double inv) {
+    const uint32_t est = (uint32_t)((double)T * 4294967296.0 * inv);
+    const int64_t rem = (int64_t)(((uint64_t)T << 32) - (uint64_t)est * W);  // in [-W, 2 W)
+    return est + (uint32_t)(rem > 0) + (uint32_t)(rem > (int64_t)W) - (uint32_t)(rem == -(int64_t)W);
+}
+
+// The rows' alias tables and compact buckets (8 words each, see common.hpp). A wave takes
+// rows_per_wave consecutive rows: all lanes fill the masses q from the sorted entries,
+// a lane per row then builds the alias tables (vose_row), and the wave writes the rows'
+// buckets as one run, two lanes per bucket (its own half, its alias half) and 32 buckets
+// per pass; the targets' record offsets, m and Shat32 come from the dense per-row table
+// k_fill writes (16 bytes a row, so that neighbouring targets share cache lines, which
+// their header units spread over the records do not). The tables of rows of up to
+// kAliasLds entries live and die in LDS (stack and alias indices in bytes); longer rows
+// have them in global scratch, indexed like the entries of C.
+// Bound by the writes of the buckets and the latency of the target look-ups, which want
+// waves: 16 rows to a wave leave 3.8 KB of LDS each. Record build of the 128^3 27-point
+// matrix: 2.48 ms with a kernel for the tables and one for the buckets (thresholds and
+// indices through memory, 64-bit divisions), 2.50 with 64 rows to a wave here, 2.20 with
+// 32, 2.03 with 16, 2.12 with 8; random matrix of 262144 rows 335 -> 281 us. The kernels
+// alone on the 160^3 records (3.4 GB of buckets): 0.96 + 1.84 ms before, 1.95 ms now.
+__global__ void __launch_bounds__(64) k_buckets32(int64_t n, const uint32_t *__restrict__ mrow,
+                                                  const uint32_t *__restrict__ roff32,
+                                                  const int64_t *__restrict__ cptr, const uint2 *__restrict__ sorted,
+                                                  const uint4 *__restrict__ tinfo, uint32_t *thr_g, int32_t *stk_g,
+                                                  int32_t *ali_g, uint32_t *__restrict__ rec32, int rows_per_wave) {
+    __shared__ uint32_t q_l[kAliasLds * kAliasPitch];
+    __shared__ uint8_t st_l[kAliasLds * kAliasPitch];
+    __shared__ uint8_t al_l[kAliasLds * kAliasPitch];
+    __shared__ uint32_t pm[kAliasRows + 1], po[kAliasRows], ws[kAliasRows];
+    __shared__ int64_t pb[kAliasRows];
+    __shared__ double wi[kAliasRows];
+    const int lane = threadIdx.x;
+    const int64_t wstride = (int64_t)gridDim.x * rows_per_wave;
+    for (int64_t r0 = (int64_t)blockIdx.x * rows_per_wave; r0 < n; r0 += wstride) {
         const int64_t r = r0 + lane;
         const bool mine = lane < rows_per_wave && r < n;
         const uint32_t m = mine ? mrow[r] : 0u;
+        const int64_t base = mine ? cptr[r] : 0;
+        const uint32_t W = m > 0 ? sorted[base + m - 1].x : 1u;
         const uint32_t incl = wave_incl_scan(m);
-        pm[lane + 1] = incl;
-        if (lane == 0) pm[0] = 0u;
-        pb[lane] = mine ? cptr[r] : 0;
-        po[lane] = mine ? roff32[r] : 0u;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (lane < kAliasRows) {
+            pm[lane + 1] = incl;
+            if (lane == 0) pm[0] = 0u;
+            pb[lane] = base;
+            po[lane] = mine ? roff32[r] : 0u;
+            ws[lane] = W;
+            wi[lane] = 1.0 / (double)W;
+        }
+        __syncthreads();
         const uint32_t total = (uint32_t)__shfl((int)incl, 63, 64);
+        for (uint32_t t = lane, i = 0; t < total; t += 64) {
+            while (pm[i + 1] <= t) ++i;
+            const uint32_t k = t - pm[i], mi = pm[i + 1] - pm[i];
+            const int64_t e = pb[i] + k;
+            const uint32_t q = mi * (sorted[e].x - (k > 0 ? sorted[e - 1].x : 0u));  // m w_k <= m 2^Q <= 2^31
+            if (mi <= (uint32_t)kAliasLds)
+                q_l[k * kAliasPitch + i] = q;
+            else
+                thr_g[e] = q;
+        }
+        __syncthreads();
+        if (m > (uint32_t)kAliasLds)
+            vose_row<int32_t>(m, W, thr_g + base, stk_g + base, ali_g + base, 1);
+        else if (m > 0)
+            vose_row<uint8_t>(m, W, q_l + lane, st_l + lane, al_l + lane, kAliasPitch);
+        __syncthreads();
         const int half = lane & 1;
         int row[kBucketSlots32];
 #pragma unroll
@@ -530,32 +548,30 @@ __global__ void __launch_bounds__(256) k_buckets32(int64_t n, const uint32_t *__
                 while (pm[row[j] + 1] <= t) ++row[j];
                 const int i = row[j];
                 const uint32_t k = t - pm[i];
+                const bool in_lds = pm[i + 1] - pm[i] <= (uint32_t)kAliasLds;
                 const int64_t e = pb[i] + k;
-                const uint2 own = sorted[e];
-                const uint32_t W = sorted[pb[i] + pm[i + 1] - pm[i] - 1].x;
-                const uint32_t T = thr_g[e];
-                const bool full = T >= W;  // no alias: both halves lead to target_j
-                const uint32_t trow = (half == 0 || full) ? own.y : sorted[pb[i] + ali_g[e]].y;
-                const uint4 ti = tinfo[trow & ~kSignBit];
-                const uint32_t tgt = ti.x | (trow & kSignBit);
-                uint32_t first;
+                const uint32_t Wi = ws[i];
+                const uint32_t T = in_lds ? q_l[k * kAliasPitch + i] : thr_g[e];
+                const bool full = T >= Wi;  // no alias: both halves lead to target_j
+                uint32_t first, trow;
                 if (half == 0) {
-                    // T' = ceil(T 2^32 / W) (< 2^32 when T < W)
-                    first = full ? 0xFFFFFFFFu : (uint32_t)((((uint64_t)T << 32) + (uint64_t)W - 1u) / (uint64_t)W);
+                    trow = sorted[e].y;
+                    first = full ? 0xFFFFFFFFu : ceil_frac32(T, Wi, wi[i]);  // T' < 2^32 when T < W
                 } else {
-                    const uint32_t prev = k > 0 ? sorted[e - 1].x : 0u;
-                    first = own.x - prev;  // w_j
+                    const uint2 own = sorted[e];
+                    const int32_t ak = in_lds ? (int32_t)al_l[k * kAliasPitch + i] : ali_g[e];
+                    trow = full ? own.y : sorted[pb[i] + ak].y;
+                    first = own.x - (k > 0 ? sorted[e - 1].x : 0u);  // w_j
                 }
-                v[j] = make_uint4(first, tgt, ti.y, ti.z);
+                const uint4 ti = tinfo[trow & ~kSignBit];
+                v[j] = make_uint4(first, ti.x | (trow & kSignBit), ti.y, ti.z);
                 dst[j] = ((size_t)po[i] + 1u + k) * kUnitWords32 + (size_t)half * 4u;
             }
 #pragma unroll
             for (int j = 0; j < kBucketSlots32; ++j)
                 if (dst[j] != ~(size_t)0) *(uint4 *)(rec32 + dst[j]) = v[j];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __syncthreads();
     }
 }
 
@@ -688,7 +704,7 @@ extern "C" mcmi_status mcmi_build_cdf_ex(const mcmi_csr_in *B, const mcmi_cdf_op
     // phase 1 (optional): ||B||_inf for the augmented diagonal
     double aug = 0.0;
     if (alpha > 0.0) {
-        k_row_abs_max<<<grid_for_lanes(n, 1, 2048), 256, 0, s>>>(n, B->row_ptr_dev, B->val_dev, norm_bits);
+        k_row_abs_max<<<(unsigned)((n + 63) / 64 < 8192 ? (n + 63) / 64 : 8192), 64, 0, s>>>(n, B->nnz, B->row_ptr_dev, B->val_dev, norm_bits);
         TRY(hipGetLastError());
         unsigned long long hb = 0;
         TRY(hipMemcpyAsync(&hb, norm_bits, sizeof(hb), hipMemcpyDeviceToHost, s));
@@ -787,14 +803,12 @@ extern "C" mcmi_status mcmi_build_cdf_ex(const mcmi_csr_in *B, const mcmi_cdf_op
     TRY(dev_alloc((void **)&qs, (size_t)(htot[1] > 0 ? htot[1] : 1) * sizeof(uint32_t), s));
     TRY(dev_alloc((void **)&stk, (size_t)(htot[1] > 0 ? 2 * htot[1] : 2) * sizeof(int32_t), s));
     {
-        int64_t ab = (n + 63) / 64;
-        if (ab > 32768) ab = 32768;
         int32_t *ali = stk + (htot[1] > 0 ? htot[1] : 1);
-        k_alias<<<(unsigned)ab, 64, 0, s>>>(n, cdf->mrow, cptr, sorted, qs, stk, ali);
-        TRY(hipGetLastError());
-        const int rpw = rows_per_wave(n);
-        k_buckets32<<<grid_for_waves(n, rpw), 256, 0, s>>>(n, cdf->mrow, cdf->roff, cptr, sorted, qs, ali, tinfo,
-                                                           cdf->rec32, rpw);
+        const int rpw = rows_per_wave(n) < kAliasRows ? rows_per_wave(n) : kAliasRows;
+        int64_t waves = (n + rpw - 1) / rpw;
+        if (waves > 65536) waves = 65536;
+        k_buckets32<<<(unsigned)waves, 64, 0, s>>>(n, cdf->mrow, cdf->roff, cptr, sorted, tinfo, qs, stk, ali,
+                                                   cdf->rec32, rpw);
     }
     TRY(hipGetLastError());
     unsigned long long hnorm = 0;
