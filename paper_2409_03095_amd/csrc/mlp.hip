@@ -675,14 +675,16 @@ extern "C" mcmi_status mcmi_mlp_adam_step(mcmi_mlp *net, const float *grad_dev, 
 // kCand doublings, or every midpoint that the next kDepth halvings can reach; the last
 // workgroup to arrive then takes the same decisions, in the same order, as a
 // sequential loop would, and ends the search once a halving changes nothing. At
-// 1M rows that is about 20 working passes of 23 us instead of 160 passes of 15 us, each
-// with a one-thread launch behind it (allocation 5.2 -> 0.55 ms). Non-finite
+// 1M rows that is about 15 working passes of 17 us (26 with each candidate's sum taken by
+// wave shuffles, one candidate after the other) instead of 160 passes of 15 us, each
+// with a one-thread launch behind it (allocation 5.2 -> 0.35 ms). Non-finite
 // predictions fall back to the uniform allocation N_r = max(1, floor(budget / sum_r cost_r)).
 namespace mcmi {
 namespace {
 
 constexpr int kDepth = 4, kCand = (1 << kDepth) - 1;
 constexpr int kAllocBlocks = 512;  // most workgroups of a pass
+constexpr int kSumPitch = 260;     // 4 more than 256: the 16 candidates of a wave's reads hit distinct banks
 constexpr int kDoublings = 101;    // hi reaches 2^100 > 1e30
 constexpr int kPasses = (kDoublings + kCand - 1) / kCand + 100 / kDepth;
 
@@ -708,10 +710,7 @@ __device__ __forceinline__ long long block_sum_ll(long long v, long long *red) {
 }
 
 __device__ __forceinline__ int32_t chains_of(double lam, double e) {
-    double k = rint(lam * e);
-    if (!(k >= 1.0)) k = 1.0;
-    if (k > 2147483647.0) k = 2147483647.0;
-    return (int32_t)k;
+    return (int32_t)fmin(fmax(rint(lam * e), 1.0), 2147483647.0);  // 1 where lam e is NaN
 }
 
 __global__ void __launch_bounds__(256) k_alloc_prep(const float *pred, const int32_t *cost, int64_t n, double *e,
@@ -737,7 +736,7 @@ __global__ void __launch_bounds__(256) k_alloc_prep(const float *pred, const int
 // workgroup), then the last workgroup's decisions.
 __global__ void __launch_bounds__(256) k_alloc_pass(const double *__restrict__ e, const int32_t *__restrict__ cost,
                                                     int64_t n, long long budget, long long *part, AllocState *st) {
-    __shared__ long long red[kCand][4];
+    __shared__ long long each[kCand][kSumPitch], red[16][kCand + 1], tot[kCand];
     __shared__ int last;
     const int32_t phase = st->phase;
     if (phase == 2) return;
@@ -771,37 +770,51 @@ __global__ void __launch_bounds__(256) k_alloc_pass(const double *__restrict__ e
 #pragma unroll
         for (int i = 0; i < kCand; ++i) sum[i] += (long long)chains_of(lam[i], er) * (long long)c;
     }
-    const int t = threadIdx.x, w = t >> 6;
+    // 16 threads to a candidate: of a workgroup's 256 shares each adds every 16th, and of
+    // the workgroups' sums likewise
+    const int t = threadIdx.x, ci = t & 15, cg = t >> 4;
 #pragma unroll
-    for (int i = 0; i < kCand; ++i) {
-        const long long v = wave_sum(sum[i]);
-        if ((t & 63) == 0) red[i][w] = v;
+    for (int i = 0; i < kCand; ++i) each[i][t] = sum[i];
+    __syncthreads();
+    if (ci < kCand) {
+        long long v = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v += each[ci][16 * k + cg];
+        red[cg][ci] = v;
     }
     __syncthreads();
-    if (t < kCand)
-        __hip_atomic_store(part + (size_t)blockIdx.x * kCand + t, red[t][0] + red[t][1] + red[t][2] + red[t][3],
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t < kCand) {
+        long long v = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v += red[k][t];
+        __hip_atomic_store(part + (size_t)blockIdx.x * kCand + t, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     if (t == 0)
         last = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u;
     __syncthreads();
     if (!last) return;
-#pragma unroll
-    for (int i = 0; i < kCand; ++i) {
+    if (ci < kCand) {
         long long v = 0;
-        for (int b = t; b < (int)gridDim.x; b += 256)
-            v += __hip_atomic_load(part + (size_t)b * kCand + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        v = wave_sum(v);
-        if ((t & 63) == 0) red[i][w] = v;
+#pragma unroll 8
+        for (int b = cg; b < (int)gridDim.x; b += 16)
+            v += __hip_atomic_load(part + (size_t)b * kCand + ci, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        red[cg][ci] = v;
+    }
+    __syncthreads();
+    if (t < kCand) {
+        long long v = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v += red[k][t];
+        tot[t] = v;
     }
     __syncthreads();
     if (t != 0) return;
     st->arrived = 0u;
-    auto total = [&](int i) { return red[i][0] + red[i][1] + red[i][2] + red[i][3]; };
     if (phase == 0) {
         double h = st->hi;
         for (int i = 0; i < kCand; ++i) {
-            const bool fits = total(i) <= budget;
+            const bool fits = tot[i] <= budget;
             if (fits && h < 1e30) {
                 h *= 2.0;
             } else {
@@ -820,7 +833,7 @@ __global__ void __launch_bounds__(256) k_alloc_pass(const double *__restrict__ e
         const double mid = 0.5 * (l + h);
         // a midpoint that equals an end whose side is known changes nothing from here on
         settled = (mid == l && l > 0.0) || (mid == h && over);
-        if (total(node) <= budget) {
+        if (tot[node] <= budget) {
             l = mid;
             node = 2 * node + 2;
         } else {
