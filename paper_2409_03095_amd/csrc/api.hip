@@ -480,6 +480,7 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
         WalkArgs a;
         memset(&a, 0, sizeof(a));
         a.rec = cdf->rec;
+        a.lds_sort = cdf->rec_units * kUnitWords * 4u > kLdsSortBytes;
         a.rec32 = cdf->rec32;
         a.roff = cdf->roff;
         a.diag = cdf->diag;

@@ -297,8 +297,6 @@ __device__ __forceinline__ bool finish_sorted(const WalkArgs &a, int32_t *tk, do
                 const uint32_t *h = a.rec32 + (size_t)(uint32_t)key[q] * kUnitWords32;
                 rw[q] = (int32_t)h[0];
                 d[q] = *(const double *)(h + 6);
-            } else {
-                d[q] = a.diag[key[q]];
             }
             mn = min(mn, (uint32_t)key[q]);
             mx = max(mx, (uint32_t)key[q]);
@@ -316,6 +314,23 @@ __device__ __forceinline__ bool finish_sorted(const WalkArgs &a, int32_t *tk, do
     wavesort::sort_words<W>(e, lane);
 #pragma unroll
     for (int q = 0; q < W; ++q) ps[lane * W + q] = e[q];
+    if (!kCmp) {
+        // d_c in column order: neighbours share lines (in table order a row of the 100^3
+        // 27-point matrix touched a line per survivor, and the walk took 18.5 ms against 17.0)
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const int i = lane + 64 * q;
+            if (i < K) {
+                const uint32_t p = ps[i] & 255u;
+                const double acc = tv[p];
+                const double nhat = pow2 ? acc * ninv : acc / nd;
+                tv[p] = nhat / a.diag[tk[p]];
+            }
+        }
+        wave_sync();
+        return true;
+    }
 #pragma unroll
     for (int q = 0; q < W; ++q) {
         const int i = lane * W + q;
@@ -392,9 +407,10 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
     unsigned long long trans = 0, spilled = 0;
     bool spill_full = false;
 
-    if constexpr (kC == 1) {
+    if constexpr (kC == 1 && kF32) {
         // one chain per lane: a lane leaves the loop with its last chain (1024^2 grid with
-        // per-row chains 7.9 -> 7.5 ms, 33 x 31 grid 150 -> 140 us against a wave vote per step)
+        // per-row chains 7.9 -> 7.5 ms, 33 x 31 grid 150 -> 140 us against a wave vote per step;
+        // binary64 rows keep the vote: 100^3 27-point 18.5 -> 18.0 ms with it, 77^3 7.9 -> 7.8)
         while (ch[0].active)
             chain_step<kF32, kCmp, Tab>(a, ch[0], kG, N, r_off, H0, prow, ptag, k0, k1, gkeys, gvals, slots, hshift, gskeys,
                                    gsvals, gsused, spill_cnt + grp, smask, trans, spilled, spill_full);
@@ -548,7 +564,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         // binary64) and 9.4 ms (1024^2 grid, 1-96 chains) against 51.4, 21.6, 8.2 and 7.8.
         const int W = K <= 64 ? 1 : K <= 128 ? 2 : 4;
         uint32_t *ps = (uint32_t *)(tv + (Hg - 32 * W));
-        bool early = scale_now && K <= 256 && K + 32 * W <= Hg;
+        bool early = scale_now && (kCmp || !a.lds_sort) && K <= 256 && K + 32 * W <= Hg;
         if (early) {
             const double ninv = 1.0 / nd_now;
             const bool pow2 = nd_now == 1.0 || (Ng & (Ng - 1)) == 0;  // acc / N = acc (1 / N) exactly
@@ -725,17 +741,19 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
         const bool ok = fits && !row_spill_full && !row_stage_full;
         if (ok) {
             for (int i = lane; i < K; i += 64) {
-                if (early) {
-                    const uint32_t e = ps[i] & 255u;
+                int e = i;
+                if (early)
+                    e = (int)(ps[i] & 255u);
+                else if (packed)
+                    e = (int)(pk[i] & 8191u);
+                if (kCmp) {
                     a.pool_col[pos0 + i] = tk[e];
                     a.pool_val[pos0 + i] = tv[e];
-                } else if (packed) {
-                    const uint64_t e = pk[i];
-                    a.pool_col[pos0 + i] = tk[e & 8191u];
-                    a.pool_val[pos0 + i] = tv[e & 8191u];
                 } else {
-                    a.pool_col[pos0 + i] = tk[i];
-                    a.pool_val[pos0 + i] = tv[i];
+                    // not kept in L2, which the full records want (100^3 27-point, binary64:
+                    // 17.0 -> 16.9 ms; the batched FP32 walk lost 0.7 %, so not there)
+                    __builtin_nontemporal_store(tk[e], a.pool_col + pos0 + i);
+                    __builtin_nontemporal_store(tv[e], a.pool_val + pos0 + i);
                 }
             }
         }

@@ -54,6 +54,14 @@ struct WalkArgs {
     double tau;                    // 0: track every contribution
     float tau32;
     int32_t sketch_slots;          // count-sketch buckets (0 when tau == 0)
+    int32_t lds_sort;              // wavefront kernel, FP64 weights: survivors sorted in LDS
 };
+
+// Above this many bytes of full records an FP64 walk runs at the DRAM's rate, and waves that
+// leave the finalize sooner only have more rows contend for the L2: sorted in LDS instead of
+// in registers a 27-point walk of 160^3 rows (7.0 GB) took 69.5 ms against 70.7 and of 100^3
+// (1.7 GB) 16.6 against 16.7, but of 77^3 (0.8 GB) 8.06 against 7.62 and of a 1024^2 grid
+// with 1 to 96 chains (0.4 GB) 9.1 against 8.3.
+constexpr uint64_t kLdsSortBytes = 1ull << 30;
 
 }  // namespace mcmi

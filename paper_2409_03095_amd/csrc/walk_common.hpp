@@ -323,10 +323,14 @@ __device__ __forceinline__ void bucket_issue(const uint32_t *rec, uint32_t off, 
     const uint32_t f = u * m;
     b.r = __umulhi(f, W);
     const uint4 *p = (const uint4 *)(rec + ((size_t)off + 1u + j) * kUnitWords);
+    // together, before other waves' loads can push the line out of L1 (100^3 27-point, binary64
+    // walk: 18.5 -> 18.3 ms; nothing on the compact records' two loads)
+    __builtin_amdgcn_s_setprio(3);
     b.q0 = p[0];
     b.q1 = p[1];
     b.q2 = p[2];
     b.q3 = kF32 ? make_uint4(0u, 0u, 0u, 0u) : p[3];
+    __builtin_amdgcn_s_setprio(0);
 }
 
 template <bool kF32>
