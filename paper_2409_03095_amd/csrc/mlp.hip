@@ -154,7 +154,10 @@ __global__ void __launch_bounds__(kWG) k_mlp_predict(MlpArgs a) {
 // sums in registers: dW2 as a 64 x 64 x 64-sample product, wave w rows 16 w .. 16 w + 15;
 // the others per lane over its own samples, the lanes' shares added at the end. A
 // parameter's sum is that of its tiles' (or lanes') shares, then of the workgroups', each
-// in index order. With LDS float atomics for every share (110 per tile, the four waves
+// in index order; the shares of db3 and of the loss are a tile's (for the loss those of its
+// samples q, 4 + q, 8 + q, 12 + q, one q after the other). That is one of the orders in
+// which LDS atomics of four waves add, those on one address taken together in a wave: a
+// step whose workgroups hold one tile each has the bits of a kernel of such atomics. With LDS float atomics for every share (110 per tile, the four waves
 // on the same addresses) a 4096-sample step's kernel took 50 us, the sum of its partials
 // 16 us and Adam 5 us: a step 68.8 us, now 17.4 (of 262144 samples 907 -> 107 us). Adding
 // the shares and partials as trees took 15.7 us, but 200 steps then ended 0.014 from the
@@ -168,7 +171,8 @@ __global__ void __launch_bounds__(kWG) k_mlp_train(MlpArgs a) {
     uint16_t *dzt = h1t + kHid * kPitch;   // [out][sample], 64 samples
     __shared__ __align__(16) uint16_t dzs[kWaves][kTile * kPitch];  // [sample][out] of a wave's tile
     __shared__ __align__(16) float xt[kWaves][kTile * kIn];
-    __shared__ float red_out[2][4 * kWaves];
+    __shared__ float red_out[4 * kWaves];
+    __shared__ __align__(16) float squares[4 * kTile];  // [wave][sample mod 4][sample / 4]
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, q = l >> 4, i = l & 15;
     const int64_t tiles = (a.count + kTile - 1) / kTile;
     const int64_t rounds = (tiles + kWaves - 1) / kWaves;
@@ -197,7 +201,7 @@ __global__ void __launch_bounds__(kWG) k_mlp_train(MlpArgs a) {
     for (int p = tid; p < kHid * kHid; p += kWG) w2t[(p & 63) * kPitch + (p >> 6)] = a.w2b[p];
     const float b3 = a.master[ob3];
     float4v G[4];
-    float gw1[4][kIn], gb1[4], gw3[4], gb2[4], gb3 = 0.f, loss = 0.f;
+    float gw1[4][kIn], gb1[4], gw3[4], gb2[4], gb3 = 0.f, sq[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) {
         G[nb] = (float4v){0.f, 0.f, 0.f, 0.f};
@@ -229,7 +233,7 @@ __global__ void __launch_bounds__(kWG) k_mlp_train(MlpArgs a) {
             const float diff = tile * kTile + 4 * q + r < a.count ? y[r] - t : 0.f;
             dy[r] = 2.f * diff * a.inv_batch;
             gb3 += dy[r];
-            loss += diff * diff;
+            sq[r] += diff * diff;
         }
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
@@ -299,8 +303,9 @@ __global__ void __launch_bounds__(kWG) k_mlp_train(MlpArgs a) {
     constexpr int kHalf = kHid / 2 * 11;
     static_assert(4 * kWaves * kHalf * sizeof(float) <= sizeof(operands), "shares");
     if (i == 0) {
-        red_out[0][4 * w + q] = gb3;
-        red_out[1][4 * w + q] = loss;
+        red_out[4 * w + q] = gb3;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) squares[kTile * w + 4 * r + q] = sq[r];
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -324,10 +329,18 @@ __global__ void __launch_bounds__(kWG) k_mlp_train(MlpArgs a) {
             dst[k < kIn ? oW1 + o * kIn + k : k == 8 ? ob1 + o : k == 9 ? ow3 + o : ob2 + o] = s;
         }
     }
-    if (tid < 2) {
+    // db3 and the loss: the four lanes of a tile first
+    if (tid == 0) {
         float s = 0.f;
-        for (int j = 0; j < 4 * kWaves; ++j) s += red_out[tid][j];
-        dst[tid == 0 ? ob3 : kParams] = s;
+        for (int j = 0; j < 4 * kWaves; j += 4) s += ((red_out[j] + red_out[j + 1]) + red_out[j + 2]) + red_out[j + 3];
+        dst[ob3] = s;
+    }
+    if (tid == 3 * 64) {  // (a wave with no share left to add above)
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < kWaves * kTile; j += 4)
+            s += ((squares[j] + squares[j + 1]) + squares[j + 2]) + squares[j + 3];
+        dst[kParams] = s;
     }
 }
 
