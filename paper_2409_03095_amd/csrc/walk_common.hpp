@@ -102,6 +102,10 @@ struct Probe {
     static __device__ __forceinline__ bool add(int32_t *keys, double *vals, uint32_t slots, uint32_t b, int32_t k[4],
                                                int32_t key, double w) {
         int s = pick_slot(k, key);
+        // Full buckets passed. A bucket counts when it is left and not before: every search
+        // for a key covers the same ones, so that a key one lane gave up on (its sum is in
+        // the spill table) cannot be inserted here by a later search.
+        int nb = 0;
         if (kPeel) {
             bool done = false;
             if (s < 4) {
@@ -110,11 +114,13 @@ struct Probe {
                 if (done) atomicAdd(&vals[b + s], w);
             }
             if (done) return true;
-            if (s == 4) b = next(b, key, slots);
+            if (s == 4) {
+                b = next(b, key, slots);
+                nb = 1;
+            }
             read_bucket_wave(keys, b, k);
             s = pick_slot(k, key);
         }
-        int nb = kPeel ? 1 : 0;
 #pragma unroll 1
         for (;;) {
             if (s < 4) {
