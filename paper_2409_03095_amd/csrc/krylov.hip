@@ -78,6 +78,16 @@ __device__ __forceinline__ double total(const Scalars &c, int which) {
 
 __device__ __forceinline__ bool first_thread() { return blockIdx.x == 0 && threadIdx.x == 0; }
 
+// The status, the same in all of a workgroup's waves, for the kernels in which workgroup 0
+// may end the solve: waves that read it one by one could return in part, and the others
+// would then add up sums that the missing waves have not written.
+__device__ __forceinline__ int32_t group_status(const Scalars &c) {
+    __shared__ int32_t status;
+    if (threadIdx.x == 0) status = c.st->status;
+    __syncthreads();
+    return status;
+}
+
 // (workgroup 0) the solve ends with `status` after `it` iterations
 __device__ __forceinline__ void end_solve(const Scalars &c, int32_t status, int64_t it) {
     c.st->it = it;
@@ -114,7 +124,7 @@ __global__ void __launch_bounds__(256) k_residual(int64_t n, const double *__res
 __global__ void __launch_bounds__(256) k_dir(int64_t n, int64_t it, const double *__restrict__ r,
                                              const double *__restrict__ v, double *__restrict__ p,
                                              double *__restrict__ x, Scalars c) {
-    const int32_t status = c.st->status;
+    const int32_t status = group_status(c);
     if (status != kRun && status != kZeroRhs) return;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -161,7 +171,7 @@ __global__ void __launch_bounds__(256) k_rhat_v(int64_t n, const double *__restr
 // alpha = rho / (rhat . v); s = r - alpha v; ||s||^2
 __global__ void __launch_bounds__(256) k_half(int64_t n, int64_t it, const double *__restrict__ r,
                                               const double *__restrict__ v, double *__restrict__ sv, Scalars c) {
-    if (c.st->status != kRun) return;
+    if (group_status(c) != kRun) return;
     const double rv = total(c, kRhatV);
     if (rv == 0.0) {
         if (first_thread()) end_solve(c, kBreakdown, it);
@@ -182,7 +192,7 @@ __global__ void __launch_bounds__(256) k_half(int64_t n, int64_t it, const doubl
 // t . s and t . t, unless the half step has converged
 __global__ void __launch_bounds__(256) k_t_dots(int64_t n, int64_t it, const double *__restrict__ t,
                                                 const double *__restrict__ sv, Scalars c) {
-    if (c.st->status != kRun) return;
+    if (group_status(c) != kRun) return;
     const double ss = total(c, kSS);
     if (sqrt(ss) <= c.rtol * c.st->bnrm) {
         if (first_thread()) {
@@ -209,7 +219,7 @@ __global__ void __launch_bounds__(256) k_step(int64_t n, int64_t it, const doubl
                                               const double *__restrict__ shat, const double *__restrict__ sv,
                                               const double *__restrict__ t, const double *__restrict__ rhat,
                                               double *__restrict__ x, double *__restrict__ r, Scalars c) {
-    const int32_t status = c.st->status;
+    const int32_t status = group_status(c);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (status == kHalf && c.st->half_it == it) {

@@ -14,6 +14,14 @@
 #define __host__
 #define __global__
 #define __forceinline__ inline
+#define __launch_bounds__(...)
+#define __shared__ static
+
+struct dim3 {
+    unsigned x, y, z;
+};
+extern dim3 threadIdx, blockIdx, blockDim, gridDim;
+void __syncthreads();
 
 typedef int hipError_t;
 typedef void *hipStream_t;
@@ -75,3 +83,5 @@ T __shfl(T, int, int = 64);
 #define __builtin_amdgcn_mbcnt_hi(a, b) ((a) ^ (b))
 #define __builtin_amdgcn_mbcnt_lo(a, b) ((a) ^ (b))
 #define __atomic_load_n(p, order) (*(p))
+#define __HIP_MEMORY_SCOPE_SYSTEM 0
+#define __hip_atomic_store(p, v, order, scope) (*(p) = (v))
