@@ -229,7 +229,9 @@ __device__ __forceinline__ void select_top(const WalkArgs &a, int32_t *tk, doubl
             nh[q] = tv[i] / nd;
             double t = fabs(nh[q]);
             if (a.filter_m) t = fabs(nh[q] / (kCmp ? diag_of_c(a.rec32, (uint32_t)key[q]) : a.diag[key[q]]));
-            b[q] = key[q] == kg ? ~0ull >> 1 : (uint64_t)__double_as_longlong(t);  // the diagonal first
+            // the diagonal first; 1 more than the value's bits, so that a value of zero (M_rc may
+            // underflow) is not taken for one of the places past the survivors
+            b[q] = key[q] == kg ? ~0ull >> 1 : (uint64_t)__double_as_longlong(t) + 1u;
         }
     }
     wave_sync();

@@ -68,9 +68,17 @@ T atomicAdd(T *p, U v) {
     return was;
 }
 
-// wave operations: declared for the headers, not modelled
+inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
+inline long long __double_as_longlong(double d) {
+    long long b;
+    memcpy(&b, &d, 8);
+    return b;
+}
+
+// wave operations: defined by the models that need them
 int __lane_id();
 uint64_t __ballot(int);
+uint32_t mask_bits_below(uint64_t mask);
 template <typename T>
 T __shfl_xor(T, int, int = 64);
 template <typename T>
@@ -80,8 +88,8 @@ T __shfl(T, int, int = 64);
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_wave_barrier() ((void)0)
 #define __builtin_amdgcn_s_setprio(p) ((void)0)
-#define __builtin_amdgcn_mbcnt_hi(a, b) ((a) ^ (b))
-#define __builtin_amdgcn_mbcnt_lo(a, b) ((a) ^ (b))
+#define __builtin_amdgcn_mbcnt_hi(m, below) (mask_bits_below((uint64_t)(m) << 32) + (below))
+#define __builtin_amdgcn_mbcnt_lo(m, below) (mask_bits_below((uint64_t)(m)) + (below))
 #define __atomic_load_n(p, order) (*(p))
 #define __HIP_MEMORY_SCOPE_SYSTEM 0
 #define __hip_atomic_store(p, v, order, scope) (*(p) = (v))
