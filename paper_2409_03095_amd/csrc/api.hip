@@ -502,7 +502,7 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
         a.filter_m = p->filter == MCMI_FILTER_M;
         a.topk = p->topk;
         a.hash_slots = H;
-        a.hash_shift = 32 - __builtin_ctz((unsigned)H);
+        a.hash_shift = table_shift(H);
         a.row_lanes = block_kernel ? 0 : lanes;
         a.lane_chains = (!block_kernel && lanes == 64) ? shape.lane_chains : 1;
         a.queue_ctr = qctr;

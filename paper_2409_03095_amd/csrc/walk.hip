@@ -871,6 +871,11 @@ hipError_t launch_walk(const WalkArgs &a, bool f32, int blocks, int waves, hipSt
         return hipErrorInvalidValue;
     if (a.lane_chains == 2 && a.row_lanes != 0 && a.row_lanes != 64) return hipErrorInvalidValue;
     if (f32 && !a.rec32) return hipErrorInvalidValue;
+    // only the small-table instance takes tables that are no power of two
+    const bool one_row = a.row_lanes == 0 || a.row_lanes == 64;
+    const bool wide = one_row && a.lane_chains != 2 && walk_wide(f32, a.topk > 0, a.hash_slots);
+    if (a.hash_slots < 64 || ((a.hash_slots & (a.hash_slots - 1)) != 0 && !(wide && a.hash_slots % 4 == 0)))
+        return hipErrorInvalidValue;
     if (a.topk > 0)
         return f32 ? launch_walk_t<true, true, true>(a, blocks, waves, s)
                    : launch_walk_t<false, false, true>(a, blocks, waves, s);

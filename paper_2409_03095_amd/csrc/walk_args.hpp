@@ -8,6 +8,11 @@ namespace mcmi {
 // 848 slots of 12 bytes and 64 bytes of counters.
 constexpr int kWideSlots = 848;
 
+// Shift that takes a 32-bit hash to a slot of a power-of-two table (0, and not used, for others).
+inline int table_shift(int hash_slots) {
+    return (hash_slots & (hash_slots - 1)) ? 0 : 32 - __builtin_ctz((unsigned)hash_slots);
+}
+
 struct WalkArgs {
     const uint32_t *rec;
     const uint32_t *rec32;         // compact records (FP32 walks)
@@ -32,8 +37,9 @@ struct WalkArgs {
     int32_t filter_m;
     int32_t topk;
     int32_t pool_chunk;  // > 0: a wave reserves pool space this many entries at a time
-    int32_t hash_slots;            // power of two (wavefront kernel: all rows of a wavefront together)
-    int32_t hash_shift;            // 32 - log2(hash_slots)
+    int32_t hash_slots;            // wavefront kernel: all rows of a wavefront together. A power of two; a
+                                   // multiple of four up to kWideSlots in the small-table instance
+    int32_t hash_shift;            // table_shift(hash_slots)
     int32_t row_lanes;             // wavefront kernel: lanes per row (8, 16, 32 or 64; 0 = 64)
     int32_t lane_chains;           // wavefront kernel, 64 lanes per row: chains a lane keeps in flight (1 or 2)
     uint32_t *queue_ctr;           // 8 counters, kQueueStride elements apart
