@@ -95,7 +95,9 @@ typedef struct {
     int32_t lanes_per_row;/* 0 = automatic; 64 = one wavefront per row; 8, 16 or 32 = 64 / that
                              many rows share a wavefront (and its tables); 256, 512 or 1024 =
                              one workgroup of that many lanes per row */
-    int32_t hash_slots;   /* 0 = automatic; else LDS hash slots per row (power of two) */
+    int32_t hash_slots;   /* 0 = automatic; else LDS hash slots per row: a power of two in
+                             [64, 8192], or the 848 that an automatic run may report in
+                             mcmi_stats (1024 where the kernel wants a power of two) */
     int32_t sketch_slots; /* 0 = automatic; else count-sketch buckets per row (64..16384) */
     int32_t pool_per_row; /* 0 = automatic; else first guess of kept entries per row: rows that
                              do not fit are rerun into a second pool sized exactly */

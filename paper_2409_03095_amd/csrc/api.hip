@@ -141,6 +141,9 @@ mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, in
     if (lanes == 0) lanes = n_hint >= 384 ? 512 : (n_hint >= 192 ? 256 : 64);
     const bool block_kernel = lanes > 64;
     int H = p->hash_slots;
+    // a table size that an earlier run reported (the check below lets no other such size in),
+    // in a run whose kernel wants a power of two
+    if (H == kWideSlots && !(lanes == 64 && p->walk_prec == MCMI_WALK_F32 && p->topk <= 0 && n_typ <= 64)) H = 1024;
     if (!H && block_kernel) H = 4096;
     if (!H && lanes == 64) {
         // one row per wavefront: a row's chains reach at most N (L + 1) columns; a
@@ -258,8 +261,9 @@ mcmi_status check_walk_params(const mcmi_params *p, bool per_row_chains, const c
     if (p->pool_per_row < 0) return bad("pool_per_row must be >= 0");
     if (p->spill_slots && (p->spill_slots < 16 || (p->spill_slots & (p->spill_slots - 1))))
         return bad("spill_slots must be a power of two >= 16");
-    if (p->hash_slots && (p->hash_slots < 64 || p->hash_slots > 8192 || (p->hash_slots & (p->hash_slots - 1))))
-        return bad("hash_slots must be a power of two in [64, 8192]");
+    if (p->hash_slots && p->hash_slots != kWideSlots &&
+        (p->hash_slots < 64 || p->hash_slots > 8192 || (p->hash_slots & (p->hash_slots - 1))))
+        return bad("hash_slots must be a power of two in [64, 8192], or 848");
     if (p->sketch_slots && (p->sketch_slots < 64 || p->sketch_slots > 16384))
         return bad("sketch_slots must be in [64, 16384]");
     if (p->lanes_per_row && p->lanes_per_row != 8 && p->lanes_per_row != 16 && p->lanes_per_row != 32 &&
