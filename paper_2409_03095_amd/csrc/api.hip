@@ -13,7 +13,8 @@ namespace mcmi {
 
 size_t walk_lds_bytes(int hash_slots, int waves);
 hipError_t launch_walk(const WalkArgs &a, bool f32, int blocks, int waves, hipStream_t s);
-hipError_t walk_occupancy(bool f32, int hash_slots, int waves, int *blocks_per_cu);
+hipError_t walk_occupancy(bool f32, bool top, int row_lanes, int lane_chains, int hash_slots, int waves,
+                          int *blocks_per_cu);
 size_t walk_block_lds_bytes(int hash_slots, int sketch_slots);
 bool walk_block_supported(int lanes, int hash_slots);
 hipError_t launch_walk_block(const WalkArgs &a, bool f32, int lanes, int blocks, hipStream_t s);
@@ -454,10 +455,11 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
             blocks = std::min<int64_t>((int64_t)bpc * cus, pass_tasks);
             regions = blocks;
         } else {
-            MCMI_HIP(walk_occupancy(f32, H, waves, &bpc));
+            const int lane_chains = lanes == 64 ? shape.lane_chains : 1;
+            MCMI_HIP(walk_occupancy(f32, p->topk > 0, lanes, lane_chains, H, waves, &bpc));
             while (bpc < 1 && waves > 1) {
                 waves >>= 1;
-                MCMI_HIP(walk_occupancy(f32, H, waves, &bpc));
+                MCMI_HIP(walk_occupancy(f32, p->topk > 0, lanes, lane_chains, H, waves, &bpc));
             }
             if (bpc < 1) return fail(MCMI_ERR_CAPACITY, "mcmi_spai: hash table does not fit in LDS");
             blocks = (int64_t)bpc * cus;

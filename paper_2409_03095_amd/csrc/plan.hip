@@ -31,7 +31,8 @@ namespace mcmi {
 
 size_t walk_lds_bytes(int hash_slots, int waves);
 hipError_t launch_walk(const WalkArgs &a, bool f32, int blocks, int waves, hipStream_t s);
-hipError_t walk_occupancy(bool f32, int hash_slots, int waves, int *blocks_per_cu);
+hipError_t walk_occupancy(bool f32, bool top, int row_lanes, int lane_chains, int hash_slots, int waves,
+                          int *blocks_per_cu);
 bool walk_block_supported(int lanes, int hash_slots);
 hipError_t launch_walk_block(const WalkArgs &a, bool f32, int lanes, int blocks, hipStream_t s);
 hipError_t walk_block_occupancy(bool f32, int lanes, int hash_slots, int sketch_slots, int *bpc);
@@ -258,7 +259,9 @@ extern "C" mcmi_status mcmi_plan_create(const mcmi_cdf *cdf, const mcmi_params *
     const int waves = 4;
     int bpc = 0;
     hipError_t e = block_kernel ? walk_block_occupancy(f32, pl->shape.lanes, pl->shape.hash, pl->shape.sketch, &bpc)
-                                : walk_occupancy(f32, pl->shape.hash, waves, &bpc);
+                                : walk_occupancy(f32, p->topk > 0, pl->shape.lanes,
+                                                 pl->shape.lanes == 64 ? pl->shape.lane_chains : 1, pl->shape.hash,
+                                                 waves, &bpc);
     if (e != hipSuccess || bpc < 1) {
         mcmi_plan_free(pl);
         return fail(MCMI_ERR_CAPACITY, "mcmi_plan_create: kernel does not fit");

@@ -844,56 +844,53 @@ __global__ void __launch_bounds__(256, kWide ? 4 : 3) k_walk(WalkArgs a) {
 size_t walk_lds_bytes(int hash_slots, int waves) { return (size_t)waves * ((size_t)hash_slots * 12u + 64u); }
 
 // Whether a launch uses the four-waves-per-SIMD instance (one row per wave, one chain per lane).
-bool walk_wide(bool f32, bool top, int hash_slots) { return f32 && !top && hash_slots <= kWideSlots; }
-
-template <bool kF32, bool kCmp, bool kTop>
-hipError_t launch_walk_t(const WalkArgs &a, int blocks, int waves, hipStream_t s) {
-    const size_t lds = walk_lds_bytes(a.hash_slots, waves);
-    switch (a.row_lanes) {
-        case 8: k_walk<kF32, 8, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a); break;
-        case 16: k_walk<kF32, 16, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a); break;
-        case 32: k_walk<kF32, 32, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a); break;
-        default:
-            if (a.lane_chains == 2)
-                k_walk<kF32, 64, 2, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a);
-            else if (kF32 && !kTop && walk_wide(true, false, a.hash_slots))
-                k_walk<kF32, 64, 1, kCmp, kTop, kF32 && !kTop><<<blocks, waves * 64, lds, s>>>(a);
-            else
-                k_walk<kF32, 64, 1, kCmp, kTop, false><<<blocks, waves * 64, lds, s>>>(a);
-            break;
-    }
-    return hipGetLastError();
+bool walk_wide(bool f32, bool top, int row_lanes, int lane_chains, int hash_slots) {
+    return f32 && !top && (row_lanes == 0 || row_lanes == 64) && lane_chains != 2 && hash_slots <= kWideSlots;
 }
 
+using WalkKernel = void (*)(WalkArgs);
+
 // FP32 walks read the compact records, FP64 walks the full ones (which carry Shat64).
+template <bool kF32, bool kTop>
+WalkKernel walk_kernel_t(int row_lanes, int lane_chains, int hash_slots) {
+    switch (row_lanes) {
+        case 8: return k_walk<kF32, 8, 1, kF32, kTop, false>;
+        case 16: return k_walk<kF32, 16, 1, kF32, kTop, false>;
+        case 32: return k_walk<kF32, 32, 1, kF32, kTop, false>;
+        default: break;
+    }
+    if (lane_chains == 2) return k_walk<kF32, 64, 2, kF32, kTop, false>;
+    if (walk_wide(kF32, kTop, row_lanes, lane_chains, hash_slots)) return k_walk<kF32, 64, 1, kF32, kTop, kF32 && !kTop>;
+    return k_walk<kF32, 64, 1, kF32, kTop, false>;
+}
+
+// The instance that runs a launch; its registers and tables set how many workgroups a CU holds.
+WalkKernel walk_kernel(bool f32, bool top, int row_lanes, int lane_chains, int hash_slots) {
+    if (top)
+        return f32 ? walk_kernel_t<true, true>(row_lanes, lane_chains, hash_slots)
+                   : walk_kernel_t<false, true>(row_lanes, lane_chains, hash_slots);
+    return f32 ? walk_kernel_t<true, false>(row_lanes, lane_chains, hash_slots)
+               : walk_kernel_t<false, false>(row_lanes, lane_chains, hash_slots);
+}
+
 hipError_t launch_walk(const WalkArgs &a, bool f32, int blocks, int waves, hipStream_t s) {
     if (a.row_lanes != 0 && a.row_lanes != 8 && a.row_lanes != 16 && a.row_lanes != 32 && a.row_lanes != 64)
         return hipErrorInvalidValue;
     if (a.lane_chains == 2 && a.row_lanes != 0 && a.row_lanes != 64) return hipErrorInvalidValue;
     if (f32 && !a.rec32) return hipErrorInvalidValue;
     // only the small-table instance takes tables that are no power of two
-    const bool one_row = a.row_lanes == 0 || a.row_lanes == 64;
-    const bool wide = one_row && a.lane_chains != 2 && walk_wide(f32, a.topk > 0, a.hash_slots);
+    const bool top = a.topk > 0, wide = walk_wide(f32, top, a.row_lanes, a.lane_chains, a.hash_slots);
     if (a.hash_slots < 64 || ((a.hash_slots & (a.hash_slots - 1)) != 0 && !(wide && a.hash_slots % 4 == 0)))
         return hipErrorInvalidValue;
-    if (a.topk > 0)
-        return f32 ? launch_walk_t<true, true, true>(a, blocks, waves, s)
-                   : launch_walk_t<false, false, true>(a, blocks, waves, s);
-    return f32 ? launch_walk_t<true, true, false>(a, blocks, waves, s)
-               : launch_walk_t<false, false, false>(a, blocks, waves, s);
+    const WalkKernel k = walk_kernel(f32, top, a.row_lanes, a.lane_chains, a.hash_slots);
+    k<<<blocks, waves * 64, walk_lds_bytes(a.hash_slots, waves), s>>>(a);
+    return hipGetLastError();
 }
 
-hipError_t walk_occupancy(bool f32, int hash_slots, int waves, int *blocks_per_cu) {
-    // the other instances differ only in loop bounds; the 64-lane one stands for all
-    const size_t lds = walk_lds_bytes(hash_slots, waves);
-    if (walk_wide(f32, false, hash_slots))
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<true, 64, 1, true, false, true>,
-                                                            waves * 64, lds);
-    if (f32)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<true, 64, 1, true, false, false>,
-                                                            waves * 64, lds);
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_walk<false, 64, 1, false, false, false>,
-                                                        waves * 64, lds);
+hipError_t walk_occupancy(bool f32, bool top, int row_lanes, int lane_chains, int hash_slots, int waves,
+                          int *blocks_per_cu) {
+    const WalkKernel k = walk_kernel(f32, top, row_lanes, lane_chains, hash_slots);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, waves * 64, walk_lds_bytes(hash_slots, waves));
 }
 
 }  // namespace mcmi
