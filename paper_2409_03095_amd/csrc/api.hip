@@ -300,6 +300,14 @@ mcmi_status read_chain_counts(const mcmi_cdf *cdf, const mcmi_params *p, const i
     return MCMI_OK;
 }
 
+// A pool of exactly topk entries per row has no room for what chunked reservations leave
+// unused (ends of chunks, each wavefront's last chunk): the rows that then did not fit were
+// walked again. An eighth and a chunk per wavefront more, as far as `most` allows.
+int64_t pool_with_slack(int64_t cap, int64_t most, int64_t wavefronts) {
+    const int64_t want = cap + cap / 8 + wavefronts * (int64_t)pool_chunk_for(cap, wavefronts);
+    return std::max(cap, std::min(want, most));
+}
+
 // Rows per wavefront and HBM overflow slots per region of a launch. Unless
 // given, the wavefront kernel's overflow table has room for every column a
 // row's chains can reach, N_max (L + 1), shared out among the rows of a
@@ -401,13 +409,14 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
     int64_t per_row = p->pool_per_row ? p->pool_per_row : std::max(h_row / 4, std::min(h_row, 256));
     if (!p->pool_per_row && p->topk > 0) per_row = std::min<int64_t>(per_row, p->topk);  // exact bound
     int64_t pool_cap = n_tasks * per_row;
-    pool_cap = std::min<int64_t>(pool_cap, (int64_t)1 << 31);
+    int64_t pool_most = (int64_t)1 << 31;
     if (!p->pool_per_row) {
         size_t free_b = 0, total_b = 0;
         if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b > 0)
-            pool_cap = std::min<int64_t>(pool_cap, (int64_t)(free_b / 4 / 12));  // at most a quarter of free HBM
-        pool_cap = std::max<int64_t>(pool_cap, 1 << 16);
+            pool_most = std::min<int64_t>(pool_most, (int64_t)(free_b / 4 / 12));  // at most a quarter of free HBM
     }
+    pool_cap = std::min<int64_t>(pool_cap, pool_most);
+    if (!p->pool_per_row) pool_cap = std::max<int64_t>(pool_cap, 1 << 16);
     pool_cap = std::max<int64_t>(pool_cap, 1);
     uint64_t retries = 0;
 
@@ -466,12 +475,8 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
             if (blocks * waves > pass_tasks) blocks = std::max<int64_t>(1, (pass_tasks + waves - 1) / waves);
             regions = blocks * waves;
         }
-        if (pass == 0 && !block_kernel && !p->pool_per_row && p->topk > 0 && pool_cap < ((int64_t)1 << 30)) {
-            // a pool of exactly topk entries per row has no room for what chunked
-            // reservations leave unused (ends of chunks, each wavefront's last chunk): the
-            // rows that then did not fit were walked again
-            pool_cap += pool_cap / 8 + regions * (int64_t)pool_chunk_for(pool_cap, regions);
-        }
+        if (pass == 0 && !block_kernel && !p->pool_per_row && p->topk > 0 && pool_cap < ((int64_t)1 << 30))
+            pool_cap = pool_with_slack(pool_cap, pool_most, regions);
         MCMI_HIP(pool_col[pass].alloc((size_t)pool_cap * sizeof(int32_t), s));
         MCMI_HIP(pool_val[pass].alloc((size_t)pool_cap * sizeof(double), s));
         pools.col[pass] = pool_col[pass].as<int32_t>();
