@@ -74,7 +74,8 @@ __device__ __forceinline__ int pick_slot(const int32_t k[4], int32_t key) {
 // How a wavefront's table is probed.
 //  kPow2: a power of two of slots (else any multiple of four);
 //  kScatter: a key whose home bucket is full goes on 1 to 8 buckets further at a time by
-//    its hash, instead of to the next: fewer long runs of full buckets where tables fill
+//    its hash (1, 3, 5 or 7 in tables below 256 slots, so that a search visits eight
+//    different ones there too), instead of to the next: fewer long runs of full buckets where tables fill
 //    up (128-chain batched walk 21.5 -> 21.2 ms, 77^3 binary64 7.95 -> 7.83; the 160^3
 //    FP32 walk 51.3 -> 51.5, so not there);
 //  kPeel: the first probe outside the loop (1024^2 grid with small tables 6.45 -> 6.25 ms; the
@@ -85,7 +86,7 @@ struct Probe {
         return kPow2 ? hash_key(key, shift) & ~3u : home_slot(key, slots / 4u);
     }
     static __device__ __forceinline__ uint32_t next(uint32_t b, int32_t key, uint32_t slots) {
-        b += kScatter ? 4u + (((uint32_t)key * 2654435761u) & 28u) : 4u;
+        b += kScatter ? 4u + (((uint32_t)key * 2654435761u) & (slots >= 256u ? 28u : 24u)) : 4u;
         if (kPow2) return b & (slots - 1u);
         return b >= slots ? b - slots : b;
     }
