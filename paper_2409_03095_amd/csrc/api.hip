@@ -128,8 +128,9 @@ hipError_t batched_lpt_map(const mcmi_cdf *cdf, double delta, int lmax, int n_hi
 
 // Kernel shape of a run: lanes per row (64 = wavefront kernel), LDS hash slots,
 // count-sketch buckets and heavy threshold tau (0 = track every contribution).
-// n_max: the largest chain count of a row.
-mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, int n_max, int n_typ,
+// n_max, n_typ: the largest and the mean chain count of a row. reruns: rows with more entries
+// than their table are walked again (false in plans).
+mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, int n_max, int n_typ, bool reruns,
                          KernelShape &out) {
     const double m_bar = cdf->n > 0 ? (double)cdf->nnz_c / (double)cdf->n : 0.0;
     const int n_hint = p->chains >= 1 ? p->chains : 64;
@@ -158,7 +159,9 @@ mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, in
         // grid, 1-96 chains, mean 12: 7.4 -> 6.2 ms; 100^3 27-point, 24 chains: 8.6 -> 7.8; rows with more chains spill to HBM).
         // Fuller tables gain nothing: 160^3 27-point, 64 chains, 848 slots 57.1 ms against
         // 51.3 with 1024, as a fuller table and fewer L2 hits cost more than the waves give.
-        const double typical = (double)std::max(n_typ, 1) * ((double)std::max(lmax, 0) + 1.0);
+        // Without reruns the rows with most chains decide: one that keeps more entries than its
+        // table has slots is lost.
+        const double typical = reruns ? (double)std::max(n_typ, 1) * ((double)std::max(lmax, 0) + 1.0) : reach;
         if (p->walk_prec == MCMI_WALK_F32 && p->topk <= 0 && n_typ <= 64 && H > kWideSlots && typical <= kWideSlots)
             H = kWideSlots;
     }
@@ -388,7 +391,7 @@ extern "C" mcmi_status mcmi_spai(const mcmi_cdf *cdf, const mcmi_params *p, cons
     const int n_hint = p->chains >= 1 ? p->chains : 64;
     KernelShape shape;
     {
-        const mcmi_status sst = choose_shape(cdf, p, lmax, n_max, n_typ, shape);
+        const mcmi_status sst = choose_shape(cdf, p, lmax, n_max, n_typ, true, shape);
         if (sst != MCMI_OK) return sst;
     }
     const bool block_kernel = shape.lanes > 64;

@@ -175,7 +175,7 @@ struct KernelShape {
 };
 struct mcmi_cdf;
 namespace mcmi {
-mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, int n_max, int n_typ,
+mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, int n_max, int n_typ, bool reruns,
                          KernelShape &out);
 // Checks shared by every walk launch (api.hip).
 mcmi_status check_walk_params(const mcmi_params *p, bool per_row_chains, const char *who);

@@ -240,7 +240,7 @@ extern "C" mcmi_status mcmi_plan_create(const mcmi_cdf *cdf, const mcmi_params *
     pl->cap = nnz_capacity;
     pl->pool_cap = nnz_capacity;
     pl->lmax = lmax;
-    mcmi_status sst = choose_shape(cdf, p, lmax, n_max, n_typ, pl->shape);
+    mcmi_status sst = choose_shape(cdf, p, lmax, n_max, n_typ, false, pl->shape);
     if (sst != MCMI_OK) {
         delete pl;
         return sst;
