@@ -41,8 +41,10 @@ using namespace walkdev;
 // [lo, hi) is the wave's current chunk. The chunk sets the locality of an XCD's
 // rows in flight (about chunk x its wavefronts consecutive rows of the schedule)
 // against the atomics on the queue counters: on the 160^3 27-point walk chunks of
-// 2, 3, 4, 8 and 16 rows took 63.0, 61.9, 61.7, 62.2 and 71.5 ms.
-constexpr int kTaskChunk = 4;
+// 2, 3, 4, 8 and 16 rows took 63.0, 61.9, 61.7, 62.2 and 71.5 ms. Binary64 walks that run at
+// the DRAM's rate (lds_sort) take kTaskChunkDram: chunks of 2, 3 and 4 rows took 70.9, 69.2 and
+// 69.7 ms there (160^3 27-point), 35.9, 35.3 and 35.4 (128^3), 60.8, 59.9 and 62.0 (2000^2 grid).
+constexpr int kTaskChunk = 4, kTaskChunkDram = 3;
 
 // Compare-exchange of a bitonic pass: a keeps the smaller word of an ascending
 // pair (up), the larger of a descending one.
@@ -59,8 +61,10 @@ __device__ __forceinline__ int64_t first_lane(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+template <bool kF32>
 __device__ __forceinline__ int64_t next_task(const WalkArgs &a, int &queue, int64_t &lo, int64_t &hi) {
     if (lo < hi) return lo++;
+    const int chunk = !kF32 && a.lds_sort ? kTaskChunkDram : kTaskChunk;
     const int lane = lane_id();
     int64_t clo = -1, chi = -1;
     if (lane == 0) {
@@ -68,10 +72,10 @@ __device__ __forceinline__ int64_t next_task(const WalkArgs &a, int &queue, int6
             const int q = (queue + tries) & 7;
             const int64_t qlo = a.n_tasks * q / 8, qhi = a.n_tasks * (q + 1) / 8;
             if (qhi > qlo && __atomic_load_n(&a.queue_ctr[q * kQueueStride], __ATOMIC_RELAXED) < (uint32_t)(qhi - qlo)) {
-                const uint32_t idx = atomicAdd(&a.queue_ctr[q * kQueueStride], (uint32_t)kTaskChunk);
+                const uint32_t idx = atomicAdd(&a.queue_ctr[q * kQueueStride], (uint32_t)chunk);
                 if ((int64_t)idx < qhi - qlo) {
                     clo = qlo + idx;
-                    chi = qlo + (int64_t)idx + kTaskChunk < qhi ? qlo + (int64_t)idx + kTaskChunk : qhi;
+                    chi = qlo + (int64_t)idx + chunk < qhi ? qlo + (int64_t)idx + chunk : qhi;
                     queue = q;
                     break;
                 }
@@ -434,7 +438,7 @@ __device__ __forceinline__ void walk_rows(const WalkArgs &a, const RowPre &cur, 
     // finalize: both latencies hide behind these rows' finalize
 #pragma unroll
     for (int g = 0; g < P; ++g) {
-        const int64_t t = next_task(a, queue, tlo, thi);
+        const int64_t t = next_task<kF32>(a, queue, tlo, thi);
         if (grp == g) row_ids(a, t, nxt);
     }
 
@@ -819,7 +823,7 @@ __global__ void __launch_bounds__(256, kWide ? 4 : 3) k_walk(WalkArgs a) {
     RowPre cur;
 #pragma unroll
     for (int g = 0; g < P; ++g) {
-        const int64_t t = next_task(a, queue, tlo, thi);
+        const int64_t t = next_task<kF32>(a, queue, tlo, thi);
         if (grp == g) row_ids(a, t, cur);
     }
     row_hdr<kF32, kCmp>(a, cur);

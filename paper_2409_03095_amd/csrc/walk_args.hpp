@@ -64,10 +64,12 @@ struct WalkArgs {
 };
 
 // Above this many bytes of full records an FP64 walk runs at the DRAM's rate, and waves that
-// leave the finalize sooner only have more rows contend for the L2: sorted in LDS instead of
-// in registers a 27-point walk of 160^3 rows (7.0 GB) took 69.5 ms against 70.7 and of 100^3
-// (1.7 GB) 16.6 against 16.7, but of 77^3 (0.8 GB) 8.06 against 7.62 and of a 1024^2 grid
-// with 1 to 96 chains (0.4 GB) 9.1 against 8.3.
+// leave the finalize sooner only have more rows contend for the L2. Sorted in LDS against in
+// registers (64 chains, alternating runs within 0.1 ms of each other): 27-point 160^3 rows
+// (7.0 GB) 69.7 and 70.8 ms, 128^3 35.4 and 36.0, 100^3 (1.7 GB) 16.5 and 16.7, a 2000^2 grid
+// (1.5 GB) 62.1 and 67.0, a random matrix of 800000 rows 69.3 and 71.6; but 77^3 (0.8 GB) 7.75
+// and 7.49, and with 24 chains 128^3 21.9 and 20.2. A batch of 60 such matrices of 24^3 to 53^3
+// rows (6.9 GB) and 20000 rows of the 128^3 set take the same time either way.
 constexpr uint64_t kLdsSortBytes = 1ull << 30;
 
 }  // namespace mcmi
