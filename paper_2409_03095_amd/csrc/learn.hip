@@ -27,92 +27,133 @@ namespace {
 
 using namespace walkdev;
 
-// P lanes per row (several rows share a wavefront), from the compact records: an
-// entry's weight, target and the target's m from its bucket, Shat64 from the
+// Features of row r by P lanes (sub: the lane's place among them), from the compact
+// records: an entry's weight, target and the target's m from its bucket, Shat64 from the
 // target's header. The sums are those of 64 strided partial sums per row added as a
-// binary tree, of which a lane keeps 64 / P. On the 1024^2 5-point grid 0.70 ms with a
-// wavefront per row on the full records, whose build (0.22 ms there, 4.9 ms on the
-// 160^3 matrix) this does without, against 0.11 ms.
+// binary tree, of which a lane keeps 64 / P.
+template <int P>
+__device__ __forceinline__ void row_features(int64_t r, int sub, const uint32_t *__restrict__ rec32,
+                                             const uint32_t *__restrict__ roff, double delta, int lmax,
+                                             float *__restrict__ feat) {
+    constexpr int T = 64 / P;
+    const uint32_t *recp = rec32 + (size_t)roff[r] * kUnitWords32;
+    const uint4 h = *(const uint4 *)recp;  // row, m, W, Shat32
+    const uint32_t m = h.y, W = h.z;
+    const double S = *(const double *)(recp + 4);
+    double ps[T], pm[T], sgn[T], smax = 0.0;
+    uint32_t wmax = 0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) ps[t] = pm[t] = sgn[t] = 0.0;
+    auto add = [&](int t, const uint4 &q0, uint32_t w, double St) {
+        const double mt = (double)q0.z;
+        ps[t] += (double)w * St;
+        pm[t] += (double)w * mt;
+        sgn[t] += (q0.y & kSignBit) ? -(double)w : (double)w;
+        smax = St > smax ? St : smax;
+        wmax = w > wmax ? w : wmax;
+    };
+    uint32_t k0 = 0;
+    if (T == 1) {  // long rows: the loads of four entries in flight
+        constexpr int U = 4;
+        for (; k0 + U * 64u <= m; k0 += U * 64u) {
+            uint4 q0[U];
+            uint32_t w[U];
+            double St[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t *e = recp + (size_t)(1u + k0 + u * 64u + sub) * kUnitWords32;
+                q0[u] = *(const uint4 *)e;
+                w[u] = e[4];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                St[u] = *(const double *)(rec32 + (size_t)(q0[u].y & ~kSignBit) * kUnitWords32 + 4);
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(0, q0[u], w[u], St[u]);
+        }
+    }
+    for (; k0 < m; k0 += 64) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const uint32_t k = k0 + (uint32_t)(t * P + sub);
+            if (k < m) {
+                const uint32_t *e = recp + (size_t)(1u + k) * kUnitWords32;
+                const uint4 q0 = *(const uint4 *)e;  // T', target, m and Shat32 of the target's row
+                add(t, q0, e[4], *(const double *)(rec32 + (size_t)(q0.y & ~kSignBit) * kUnitWords32 + 4));
+            }
+        }
+    }
+#pragma unroll
+    for (int hh = T / 2; hh > 0; hh >>= 1)
+#pragma unroll
+        for (int t = 0; t < hh; ++t) {
+            ps[t] += ps[t + hh];
+            pm[t] += pm[t + hh];
+            sgn[t] += sgn[t + hh];
+        }
+#pragma unroll
+    for (int off = P / 2; off > 0; off >>= 1) {
+        ps[0] += __shfl_xor(ps[0], off, P);
+        pm[0] += __shfl_xor(pm[0], off, P);
+        sgn[0] += __shfl_xor(sgn[0], off, P);
+        const double so = __shfl_xor(smax, off, P);
+        smax = so > smax ? so : smax;
+        const uint32_t wo = (uint32_t)__shfl_xor((int)wmax, off, P);
+        wmax = wo > wmax ? wo : wmax;
+    }
+    if (sub == 0) {
+        const double Wd = (double)W;
+        float4 f0, f1;
+        f0.x = (float)log((double)(m > 1u ? m : 1u));
+        f0.y = (float)S;
+        f0.z = m ? (float)(S * (double)wmax / Wd) : 0.f;
+        f0.w = m ? (float)(ps[0] / Wd) : 0.f;
+        f1.x = (float)smax;
+        f1.y = m ? (float)(pm[0] / Wd) : 0.f;
+        f1.z = (m && S > 0.0) ? (float)(fabs(sgn[0]) / Wd) : 0.f;
+        double f7;
+        if (S > 0.0 && S < 1.0 && delta > 0.0) {
+            const double l = log(delta) / log(S);
+            f7 = l < (double)lmax ? l : (double)lmax;
+        } else {
+            f7 = S > 0.0 ? (double)lmax : 0.0;
+        }
+        f1.w = (float)f7;
+        float *f = feat + 8 * r;
+        f[0] = f0.x;
+        f[1] = f0.y;
+        f[2] = f0.z;
+        f[3] = f0.w;
+        f[4] = f1.x;
+        f[5] = f1.y;
+        f[6] = f1.z;
+        f[7] = f1.w;
+    }
+}
+
+// P lanes per row, several rows to a wavefront; a row of more than kFeatureWide entries is
+// left to the whole wavefront. On the 1024^2 5-point grid 0.70 ms with a wavefront per row on
+// the full records, whose build (0.22 ms there, 4.9 ms on the 160^3 matrix) this does
+// without, against 0.09 ms. Random matrix of 20000 rows, one of 3000 entries: 23 us that way,
+// 79 us with its 16 lanes for that row, 34 us with the wavefront, 17 us with four loads ahead.
+constexpr uint32_t kFeatureWide = 256;
+
 template <int P>
 __global__ void __launch_bounds__(256) k_features(int64_t n, const uint32_t *__restrict__ rec32,
                                                   const uint32_t *__restrict__ roff, double delta, int lmax,
                                                   float *__restrict__ feat) {
-    constexpr int T = 64 / P;
-    const int sub = threadIdx.x & (P - 1);
-    const int64_t group = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / P;
+    const int lane = threadIdx.x & 63, sub = threadIdx.x & (P - 1);
     const int64_t groups = ((int64_t)gridDim.x * blockDim.x) / P;
-    for (int64_t r = group; r < n; r += groups) {
-        const uint32_t *recp = rec32 + (size_t)roff[r] * kUnitWords32;
-        const uint4 h = *(const uint4 *)recp;  // row, m, W, Shat32
-        const uint32_t m = h.y, W = h.z;
-        const double S = *(const double *)(recp + 4);
-        double ps[T], pm[T], sgn[T], smax = 0.0;
-        uint32_t wmax = 0;
-#pragma unroll
-        for (int t = 0; t < T; ++t) ps[t] = pm[t] = sgn[t] = 0.0;
-        for (uint32_t k0 = 0; k0 < m; k0 += 64) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const uint32_t k = k0 + (uint32_t)(t * P + sub);
-                if (k < m) {
-                    const uint32_t *e = recp + (size_t)(1u + k) * kUnitWords32;
-                    const uint4 q0 = *(const uint4 *)e;  // T', target, m and Shat32 of the target's row
-                    const uint32_t w = e[4];
-                    const double St = *(const double *)(rec32 + (size_t)(q0.y & ~kSignBit) * kUnitWords32 + 4);
-                    const double mt = (double)q0.z;
-                    ps[t] += (double)w * St;
-                    pm[t] += (double)w * mt;
-                    sgn[t] += (q0.y & kSignBit) ? -(double)w : (double)w;
-                    smax = St > smax ? St : smax;
-                    wmax = w > wmax ? w : wmax;
-                }
-            }
+    int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / P;
+    for (; r - lane / P < n; r += groups) {  // uniform over the wave
+        bool wide = false;
+        if (r < n) {
+            wide = P < 64 && rec32[(size_t)roff[r] * kUnitWords32 + 1] > kFeatureWide;
+            if (!wide) row_features<P>(r, sub, rec32, roff, delta, lmax, feat);
         }
-#pragma unroll
-        for (int hh = T / 2; hh > 0; hh >>= 1)
-#pragma unroll
-            for (int t = 0; t < hh; ++t) {
-                ps[t] += ps[t + hh];
-                pm[t] += pm[t + hh];
-                sgn[t] += sgn[t + hh];
-            }
-#pragma unroll
-        for (int off = P / 2; off > 0; off >>= 1) {
-            ps[0] += __shfl_xor(ps[0], off, P);
-            pm[0] += __shfl_xor(pm[0], off, P);
-            sgn[0] += __shfl_xor(sgn[0], off, P);
-            const double so = __shfl_xor(smax, off, P);
-            smax = so > smax ? so : smax;
-            const uint32_t wo = (uint32_t)__shfl_xor((int)wmax, off, P);
-            wmax = wo > wmax ? wo : wmax;
-        }
-        if (sub == 0) {
-            const double Wd = (double)W;
-            float4 f0, f1;
-            f0.x = (float)log((double)(m > 1u ? m : 1u));
-            f0.y = (float)S;
-            f0.z = m ? (float)(S * (double)wmax / Wd) : 0.f;
-            f0.w = m ? (float)(ps[0] / Wd) : 0.f;
-            f1.x = (float)smax;
-            f1.y = m ? (float)(pm[0] / Wd) : 0.f;
-            f1.z = (m && S > 0.0) ? (float)(fabs(sgn[0]) / Wd) : 0.f;
-            double f7;
-            if (S > 0.0 && S < 1.0 && delta > 0.0) {
-                const double l = log(delta) / log(S);
-                f7 = l < (double)lmax ? l : (double)lmax;
-            } else {
-                f7 = S > 0.0 ? (double)lmax : 0.0;
-            }
-            f1.w = (float)f7;
-            float *f = feat + 8 * r;
-            f[0] = f0.x;
-            f[1] = f0.y;
-            f[2] = f0.z;
-            f[3] = f0.w;
-            f[4] = f1.x;
-            f[5] = f1.y;
-            f[6] = f1.z;
-            f[7] = f1.w;
+        if (P < 64) {
+            for (uint64_t left = __ballot(wide && sub == 0); left != 0; left &= left - 1)
+                row_features<64>(r - lane / P + __builtin_ctzll(left) / P, lane, rec32, roff, delta, lmax, feat);
         }
     }
 }
