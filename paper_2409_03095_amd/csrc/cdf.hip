@@ -348,19 +348,17 @@ __global__ void __launch_bounds__(256) k_fill(int64_t n, const int64_t *__restri
 // grows up from the front, large down from the back), q (filled by the caller) and A in
 // two more, at stride sc.
 constexpr int kAliasLds = 32;    // rows up to this long keep their scratch in LDS
+// Rows longer than this have their stacks filled by the whole wave: a lane alone waits for a
+// store and a load at every entry (20000 random rows, one of 3000 entries: 1.91 -> 1.37 ms,
+// 1.73 with the alias tables in a kernel of their own; 600 dense rows 0.51 -> 0.40 ms).
+constexpr int kAliasWide = 512;
 constexpr int kAliasRows = 16;   // most rows that a wave takes together
 constexpr int kAliasPitch = 17;  // LDS words per entry index: the rows hit distinct banks
 
+// The lane's part begins with ns small and nl large entries on the stacks (vose_pairs), or
+// with none (vose_row).
 template <typename I>
-__device__ __forceinline__ void vose_row(uint32_t m, uint32_t W, uint32_t *q, I *st, I *al, int sc) {
-    int ns = 0, nl = 0;
-    for (uint32_t k = 0; k < m; ++k) {
-        al[k * sc] = (I)k;
-        if (q[k * sc] < W)
-            st[(ns++) * sc] = (I)k;
-        else
-            st[(m - 1 - nl++) * sc] = (I)k;
-    }
+__device__ __forceinline__ void vose_pairs(uint32_t m, uint32_t W, uint32_t *q, I *st, I *al, int sc, int ns, int nl) {
     while (ns > 0 && nl > 0) {
         const int sm = (int)st[(--ns) * sc];
         const int lg = (int)st[(m - nl--) * sc];
@@ -372,6 +370,19 @@ __device__ __forceinline__ void vose_row(uint32_t m, uint32_t W, uint32_t *q, I 
         else
             st[(m - 1 - nl++) * sc] = (I)lg;
     }
+}
+
+template <typename I>
+__device__ __forceinline__ void vose_row(uint32_t m, uint32_t W, uint32_t *q, I *st, I *al, int sc) {
+    int ns = 0, nl = 0;
+    for (uint32_t k = 0; k < m; ++k) {
+        al[k * sc] = (I)k;
+        if (q[k * sc] < W)
+            st[(ns++) * sc] = (I)k;
+        else
+            st[(m - 1 - nl++) * sc] = (I)k;
+    }
+    vose_pairs<I>(m, W, q, st, al, sc, ns, nl);
 }
 
 constexpr int kBucketSlots = 4;
@@ -528,7 +539,33 @@ __global__ void __launch_bounds__(64) k_buckets32(int64_t n, const uint32_t *__r
                 thr_g[e] = q;
         }
         __syncthreads();
-        if (m > (uint32_t)kAliasLds)
+        // the stacks of long rows by the whole wave, 64 entries at a time
+        int ns = 0, nl = 0;
+        for (uint64_t left = __ballot(m > (uint32_t)kAliasWide); left != 0; left &= left - 1) {
+            const int i = __builtin_ctzll(left);
+            const uint32_t mi = pm[i + 1] - pm[i], Wi = ws[i];
+            const int64_t b = pb[i];
+            int s = 0, l = 0;
+            for (uint32_t k0 = 0; k0 < mi; k0 += 64) {
+                const uint32_t k = k0 + lane;
+                const bool small = k < mi && thr_g[b + k] < Wi;
+                const uint64_t sm = __ballot(small), lg = __ballot(k < mi && !small);
+                if (k < mi) {
+                    ali_g[b + k] = (int32_t)k;
+                    stk_g[b + (small ? s + mask_rank(sm) : (int)mi - 1 - l - mask_rank(lg))] = (int32_t)k;
+                }
+                s += __popcll(sm);
+                l += __popcll(lg);
+            }
+            if (lane == i) {
+                ns = s;
+                nl = l;
+            }
+        }
+        __syncthreads();
+        if (m > (uint32_t)kAliasWide)
+            vose_pairs<int32_t>(m, W, thr_g + base, stk_g + base, ali_g + base, 1, ns, nl);
+        else if (m > (uint32_t)kAliasLds)
             vose_row<int32_t>(m, W, thr_g + base, stk_g + base, ali_g + base, 1);
         else if (m > 0)
             vose_row<uint8_t>(m, W, q_l + lane, st_l + lane, al_l + lane, kAliasPitch);
