@@ -403,9 +403,42 @@ __global__ void __launch_bounds__(256) k_round_weights(const float *master, uint
 }
 
 // mean and 1/std of each feature column (population std; 1 when the column is
-// constant): workgroup sums of x and x^2 per column, then one workgroup adds them in
-// index order. (One workgroup per column over all rows: 259 us for 200k rows, 12 us so.)
+// constant). Up to kStatRows rows a workgroup takes a column (k_column_stats). Beyond them,
+// workgroup sums of x and x^2 of all columns, which one workgroup adds in index order: with a
+// workgroup per column 7, 11, 18 and 214 us for 8000, 16000, 30000 and 200000 rows, with the
+// two launches 10, 12, 14 and 16.
 constexpr int kStatBlocks = 128;
+constexpr int64_t kStatRows = 20000;
+
+// column k's entries of norm from its sums over n rows
+__device__ __forceinline__ void put_norm(float *norm, int k, double s, double s2, int64_t n) {
+    const double mean = s / (double)n;
+    const double var = s2 / (double)n - mean * mean;
+    norm[k] = (float)mean;
+    norm[kIn + k] = var > 1e-12 ? (float)(1.0 / sqrt(var)) : 1.f;
+}
+
+__global__ void __launch_bounds__(256) k_column_stats(const float *__restrict__ feat, int64_t n, float *norm) {
+    __shared__ double red[2][256];
+    const int k = blockIdx.x, t = threadIdx.x;
+    double s = 0.0, s2 = 0.0;
+    for (int64_t r = t; r < n; r += 256) {
+        const double x = feat[r * kIn + k];
+        s += x;
+        s2 += x * x;
+    }
+    red[0][t] = s;
+    red[1][t] = s2;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+        if (t < off) {
+            red[0][t] += red[0][t + off];
+            red[1][t] += red[1][t + off];
+        }
+        __syncthreads();
+    }
+    if (t == 0) put_norm(norm, k, red[0][0], red[1][0], n);
+}
 
 __global__ void __launch_bounds__(256) k_feature_sums(const float *__restrict__ feat, int64_t n,
                                                       double *__restrict__ sums) {
@@ -439,12 +472,7 @@ __global__ void __launch_bounds__(64) k_feature_stats(const double *__restrict__
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
     const double s2 = __shfl(v, (k & 7) + kIn, 64);
-    if (threadIdx.x < kIn) {
-        const double mean = v / (double)n;
-        const double var = s2 / (double)n - mean * mean;
-        norm[k] = (float)mean;
-        norm[kIn + k] = var > 1e-12 ? (float)(1.0 / sqrt(var)) : 1.f;
-    }
+    if (threadIdx.x < kIn) put_norm(norm, k, v, s2, n);
 }
 
 }  // namespace
@@ -585,6 +613,11 @@ extern "C" mcmi_status mcmi_mlp_set_adam_state(mcmi_mlp *net, const float *adam_
 
 extern "C" mcmi_status mcmi_mlp_fit_normalization(mcmi_mlp *net, const float *feat_dev, int64_t n, void *stream) {
     if (!net || !feat_dev || n < 1) return fail(MCMI_ERR_ARG, "mcmi_mlp_fit_normalization: bad argument");
+    if (n <= kStatRows) {
+        k_column_stats<<<kIn, 256, 0, (hipStream_t)stream>>>(feat_dev, n, net->norm);
+        MCMI_HIP(hipGetLastError());
+        return MCMI_OK;
+    }
     const int blocks = (int)std::min<int64_t>((n + 255) / 256, kStatBlocks);
     k_feature_sums<<<blocks, 256, 0, (hipStream_t)stream>>>(feat_dev, n, net->sums);
     MCMI_HIP(hipGetLastError());
