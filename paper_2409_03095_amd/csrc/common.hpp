@@ -212,9 +212,8 @@ struct WaveLayout {
 WaveLayout wave_layout(const KernelShape &shape, int spill_given, int n_max, int lmax);
 }
 
-// Full records from the compact ones (cdf.hip), once per record set: every
-// consumer other than the FP32 walks of the wavefront kernel calls this first
-// (FP64 walks, the workgroup kernel, row features, pilot walks, downloads).
+// Full records from the compact ones (cdf.hip), once per record set: what reads
+// them calls this first (FP64 walks of both kernels, FP64 pilot walks, downloads).
 // Synchronises the stream the first time, so that every stream sees them.
 namespace mcmi {
 hipError_t ensure_full_records(const mcmi_cdf *cdf, hipStream_t s);

@@ -12,8 +12,8 @@
 // the solve has ended. The host queues up to kAhead iterations ahead and reads the status and
 // the iteration that launches leave in host memory. A 100 x 77 5-point grid (45 iterations)
 // took 7.4 ms with two launches, a copy and a wait per inner product, 1.44 ms with the
-// partials added by the last workgroup to arrive, and takes 1.28 ms so; a 64^3 27-point
-// stencil with its M (1024 partials to a product) took 2.9 / 1.73 / 1.06 ms.
+// partials added by the last workgroup to arrive, and takes 1.27 to 1.4 ms so; a 64^3 27-point
+// stencil with its M (1024 partials to a product) took 2.9 / 1.73 / 1.0 ms.
 #include <math.h>
 #include <string.h>
 
