@@ -97,7 +97,8 @@ typedef struct {
                              one workgroup of that many lanes per row */
     int32_t hash_slots;   /* 0 = automatic; else LDS hash slots per row: a power of two in
                              [64, 8192], or the 848 that an automatic run may report in
-                             mcmi_stats (1024 where the kernel wants a power of two) */
+                             mcmi_stats (1024 where the kernel wants a power of two, and in
+                             plans with rows that can reach more columns) */
     int32_t sketch_slots; /* 0 = automatic; else count-sketch buckets per row (64..16384) */
     int32_t pool_per_row; /* 0 = automatic; else first guess of kept entries per row: rows that
                              do not fit are rerun into a second pool sized exactly */

@@ -144,16 +144,18 @@ mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, in
     const bool block_kernel = lanes > 64;
     int H = p->hash_slots;
     // a table size that an earlier run reported (the check below lets no other such size in),
-    // in a run whose kernel wants a power of two
-    if (H == kWideSlots && !(lanes == 64 && p->walk_prec == MCMI_WALK_F32 && p->topk <= 0 && n_typ <= 64)) H = 1024;
+    // in a run whose kernel wants a power of two, or whose rows may need more and are not rerun
+    const double reach_max = (double)std::max(n_max, 1) * ((double)std::max(lmax, 0) + 1.0);
+    if (H == kWideSlots && (!(lanes == 64 && p->walk_prec == MCMI_WALK_F32 && p->topk <= 0 && n_typ <= 64) ||
+                            (!reruns && reach_max > kWideSlots)))
+        H = 1024;
     if (!H && block_kernel) H = 4096;
     if (!H && lanes == 64) {
         // one row per wavefront: a row's chains reach at most N (L + 1) columns; a
         // table of that size (128 to 1024 slots) lets more wavefronts share a CU's
         // LDS, which is what keeps enough rows in flight when rows have few chains
-        const double reach = (double)std::max(n_max, 1) * ((double)std::max(lmax, 0) + 1.0);
         H = 128;
-        while (H < 1024 && (double)H < reach) H *= 2;
+        while (H < 1024 && (double)H < reach_max) H *= 2;
         // FP32 walks of rows that typically reach at most kWideSlots columns take a table of
         // that size at most: a CU then holds sixteen wavefronts instead of twelve (1024^2
         // grid, 1-96 chains, mean 12: 7.4 -> 6.2 ms; 100^3 27-point, 24 chains: 8.6 -> 7.8; rows with more chains spill to HBM).
@@ -161,7 +163,7 @@ mcmi_status choose_shape(const mcmi_cdf *cdf, const mcmi_params *p, int lmax, in
         // 51.3 with 1024, as a fuller table and fewer L2 hits cost more than the waves give.
         // Without reruns the rows with most chains decide: one that keeps more entries than its
         // table has slots is lost.
-        const double typical = reruns ? (double)std::max(n_typ, 1) * ((double)std::max(lmax, 0) + 1.0) : reach;
+        const double typical = reruns ? (double)std::max(n_typ, 1) * ((double)std::max(lmax, 0) + 1.0) : reach_max;
         if (p->walk_prec == MCMI_WALK_F32 && p->topk <= 0 && n_typ <= 64 && H > kWideSlots && typical <= kWideSlots)
             H = kWideSlots;
     }

@@ -9,8 +9,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
+@pytest.mark.parametrize("slots", [0, 848])  # automatic; what an eager run reported
 @pytest.mark.parametrize("hot", [70, 90, 105])
-def test_plan_keeps_the_rows_with_most_chains(hot):
+def test_plan_keeps_the_rows_with_most_chains(hot, slots):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2409_03095_amd import mcmi as mc
@@ -23,6 +24,7 @@ def test_plan_keeps_the_rows_with_most_chains(hot):
     p = mc.params(seed=8, chains=1, delta=1e-4, eps=1e-9, walk_prec=32, max_len=25)
     res = mc.spai(cdf, p, chains_per_row=cpr)
     rp, col, _ = res.to_numpy()
+    p.hash_slots = slots
     plan = mc.Plan(cdf, p, 400 * B.n, chains_per_row=cpr)
     plan.launch(8)
     out, st, overflow = plan.result()
